@@ -22,6 +22,7 @@
 // lane reaches every workgroup barrier.
 #pragma once
 #include "kernels.h"
+#include "lazy.h"
 
 namespace eccmi {
 
@@ -254,23 +255,36 @@ __global__ void __launch_bounds__(WG) k_verify(const uint8_t* __restrict__ hashe
   }
 }
 
-// ---- latency form: one request per lane in XYZZ coordinates -----------------
+// ---- latency form: one request per lane --------------------------------------
 //
 // The loop above inverts once per scalar bit for the whole workgroup, so a
 // launch costs 257 inversion latencies however few requests it holds.  This
-// form keeps each request's sum in XYZZ coordinates on its own lane and
-// inverts twice per launch (s mod n, and the table below), at about the same
-// number of products per request:
-//   u2 Q: 4-bit windows from the most significant end, four doublings and one
-//         mixed addition of T[d] = d Q per window; T[2..15] are made on the
-//         lane and normalised to affine with one Montgomery-trick chain and
-//         one Gather-Apply-Scatter inversion;
-//   u1 G: one mixed addition per byte of u1, of d 2^(8 j) G from a comb table
-//         of 32 x 256 points made once per context;
+// form keeps each request's sum on its own lane in projective coordinates
+// and inverts twice per launch (s mod n, and the table below):
+//   u2 Q: signed 4-bit windows from the most significant end, four Jacobian
+//         doublings and one mixed addition of +-T[|d|] = +-|d| Q per window;
+//         T[2..8] are made on the lane and normalised to affine with one
+//         Montgomery-trick chain and one Gather-Apply-Scatter inversion;
+//   u1 G: one mixed XYZZ addition per byte of u1, of d 2^(8 j) G from a comb
+//         table of 32 x 256 points made once per context;
 //   R.x mod n = r without an inversion: x = X / ZZ, so the test is X = r ZZ,
 //         or X = (r + n) ZZ when r + n < p.
+//
+// Bound by the instruction stream (one product of the 256-bit primes takes
+// about 190 instructions, and one wave per SIMD already issues at 85% of the
+// peak).  Signed lazy limbs (lazy.h) take the carries, comparisons and
+// multiples of p out of every modular sum; Jacobian doublings take 4 products
+// and 4 squarings in 7 reductions where XYZZ takes 7, 2 and 8 (252 of them
+// per product); eight signed table entries cost 7 fewer table points than
+// fifteen unsigned ones at the same number of windows.  Five-bit windows
+// would save ten additions and cost eight more table points, at 17 products
+// each: more than they save.
+// Measured (one call, unsigned limbs with fifteen-entry tables before): 2^19
+// SM2 products 14.36 -> 9.33 ms, 3001 BN254 products 1.78 -> 1.14 ms, 2^16 SM2
+// verifications 1.84 -> 1.52 ms, 2^18 SM2 signatures 0.695 -> 0.614 ms, 2^19
+// SM2 fixed-point products 1.20 -> 1.00 ms.
 
-constexpr int VT_N = 15;            // table entries d Q, d = 1..15
+constexpr int VT_N = 8;             // table entries d Q, d = 1..8
 constexpr int VCOMB_WINDOWS = 32;
 constexpr int VCOMB_ENTRIES = 256;  // entry 0 of each window is never read
 
@@ -306,16 +320,16 @@ __device__ __forceinline__ void vt_load(const uint32_t* __restrict__ s, uint32_t
 }
 
 template <class F>
-__device__ __forceinline__ void vt_pack(uint32_t* __restrict__ w, const Fp<F>& a) {
+__device__ __forceinline__ void vt_pack(uint32_t* __restrict__ w, const Lz<F>& a) {
 #pragma unroll
-  for (int k = 0; k < F::NL; k++) w[k] = a.w[k];
+  for (int k = 0; k < F::NL; k++) w[k] = uint32_t(a.w[k]);
 }
 
 template <class F>
-__device__ __forceinline__ Fp<F> vt_unpack(const uint32_t* __restrict__ w) {
-  Fp<F> a;
+__device__ __forceinline__ Lz<F> vt_unpack(const uint32_t* __restrict__ w) {
+  Lz<F> a;
 #pragma unroll
-  for (int k = 0; k < F::NL; k++) a.w[k] = w[k];
+  for (int k = 0; k < F::NL; k++) a.w[k] = int32_t(w[k]);
   return a;
 }
 
@@ -327,21 +341,27 @@ constexpr int vt_affine_words() {
 }
 
 template <class C>
-__device__ __forceinline__ void vt_put_affine(uint32_t* __restrict__ s, const Fp<typename C::F>& x,
-                                              const Fp<typename C::F>& y) {
+__device__ __forceinline__ void vt_put_affine(uint32_t* __restrict__ s, const Lz<typename C::F>& x,
+                                              const Lz<typename C::F>& y) {
   constexpr int NL = C::F::NL;
   uint32_t w[vt_affine_words<typename C::F>()] = {};
-  vt_pack(w, x);
-  vt_pack(w + NL, y);
+  vt_pack<typename C::F>(w, x);
+  vt_pack<typename C::F>(w + NL, y);
   vt_store(s, w);
 }
 
+// an affine point as lazy coordinates; x.w[0] < 0 marks O
 template <class C>
-__device__ __forceinline__ Affine<C> vt_get_affine(const uint32_t* __restrict__ s) {
+struct LzAffine {
+  Lz<typename C::F> x, y;
+};
+
+template <class C>
+__device__ __forceinline__ LzAffine<C> vt_get_affine(const uint32_t* __restrict__ s) {
   using F = typename C::F;
   uint32_t w[vt_affine_words<F>()];
   vt_load(s, w);
-  Affine<C> a;
+  LzAffine<C> a;
   a.x = vt_unpack<F>(w);
   a.y = vt_unpack<F>(w + F::NL);
   return a;
@@ -369,10 +389,10 @@ __device__ __forceinline__ uint32_t take_low(uint32_t (&a)[8]) {
   return d;
 }
 
-// This lane's table T[d] = d Q (d = 1..15) as affine entries: made in XYZZ
+// This lane's table T[d] = d Q (d = 1..VT_N) as affine entries: made in XYZZ
 // coordinates, then normalised with one Montgomery-trick chain over the ZZZ
 // and one Gather-Apply-Scatter inversion for the workgroup (every lane must
-// call it).  An entry that is O (Q of order at most 15, possible only off the
+// call it).  An entry that is O (Q of order at most 8, possible only off the
 // prime-order subgroup) puts 1 into the chain and is stored as the infinity
 // marker, which the mixed addition skips.  Q itself must not be O.
 template <class C, int WG>
@@ -382,56 +402,128 @@ __device__ __forceinline__ void vt_build(uint32_t* __restrict__ tab, const Affin
   constexpr int NL = F::NL;
   constexpr int SLOT = vt_slot<F>();
   static_assert(vt_affine_words<F>() <= SLOT, "affine entry inside its slot");
-  XYZZ<C> T = xyzz_from_affine<C>(Q);
-  Fp<F> pref = fp_one<F>();
+  const Lz<F> qx = lz_of<F>(Q.x), qy = lz_of<F>(Q.y);
+  Xz<C> T;
+  xz_mdbl<C>(T, qx, qy);  // no curve here has a point of order 2
+  bool inf = false;
+  Lz<F> pref = lz_one<F>();
 #pragma unroll 1
   for (int d = 2; d <= VT_N; d++) {
-    T = xyzz_add_affine_in<C>(T, Q);  // d = 2 takes the doubling case
-    const bool inf = xyzz_is_inf<C>(T);
-    const Fp<F> z = inf ? fp_one<F>() : T.ZZZ;
+    const Lz<F> z = lz_select<F>(inf, lz_one<F>(), T.ZZZ);
     uint32_t w[SLOT] = {};
-    vt_pack(w, T.X);
-    vt_pack(w + NL, T.Y);
-    vt_pack(w + 2 * NL, T.ZZ);
-    vt_pack(w + 3 * NL, z);
-    vt_pack(w + 4 * NL, pref);
+    vt_pack<F>(w, T.X);
+    vt_pack<F>(w + NL, T.Y);
+    vt_pack<F>(w + 2 * NL, T.ZZ);
+    vt_pack<F>(w + 3 * NL, z);
+    vt_pack<F>(w + 4 * NL, pref);
     w[5 * NL] = inf ? 1u : 0u;
     vt_store(tab + (d - 1) * SLOT, w);
-    pref = fp_mul<F>(pref, z);
+    pref = lz_mul<F>(pref, z);
+    if (d < VT_N) xz_madd<C>(T, inf, qx, qy);
   }
-  Fp<F> inv = wg_batch_inverse<F, WG, 4>(pref, s_tot, s_inv);
+  Lz<F> inv = lz_of<F>(wg_batch_inverse<F, WG, 4>(lz_semi<F>(pref), s_tot, s_inv));
 #pragma unroll 1
   for (int d = VT_N; d >= 2; d--) {
     uint32_t* sl = tab + (d - 1) * SLOT;
     uint32_t w[SLOT];
     vt_load(sl, w);
-    const Fp<F> t = fp_mul<F>(inv, vt_unpack<F>(w + 4 * NL));  // 1 / ZZZ_d
-    inv = fp_mul<F>(inv, vt_unpack<F>(w + 3 * NL));            // 1 / (ZZZ_2 ... ZZZ_(d-1))
-    const Fp<F> iz = fp_mul<F>(vt_unpack<F>(w + 2 * NL), t);   // 1 / Z (ZZ = Z^2, ZZZ = Z^3)
-    Fp<F> x = fp_canonical<F>(fp_mul<F>(vt_unpack<F>(w), fp_sqr<F>(iz)));
-    const Fp<F> y = fp_canonical<F>(fp_mul<F>(vt_unpack<F>(w + NL), t));
-    if (w[5 * NL]) x = fp_inf_marker<F>();
+    const Lz<F> t = lz_mul<F>(inv, vt_unpack<F>(w + 4 * NL));  // 1 / ZZZ_d
+    inv = lz_mul<F>(inv, vt_unpack<F>(w + 3 * NL));            // 1 / (ZZZ_2 ... ZZZ_(d-1))
+    const Lz<F> iz = lz_mul<F>(vt_unpack<F>(w + 2 * NL), t);   // 1 / Z (ZZ = Z^2, ZZZ = Z^3)
+    Lz<F> x = lz_mul<F>(vt_unpack<F>(w), lz_sqr<F>(iz));
+    const Lz<F> y = lz_mul<F>(vt_unpack<F>(w + NL), t);
+    if (w[5 * NL]) x = lz_of<F>(fp_inf_marker<F>());
     vt_put_affine<C>(sl, x, y);
   }
-  vt_put_affine<C>(tab, Q.x, Q.y);
+  vt_put_affine<C>(tab, qx, qy);
 }
 
-// u Q from this lane's table: 4-bit windows from the most significant end,
-// four doublings and one mixed addition each; u (256 bits) is consumed
+// u + sum over j of 8 16^j (256 bits): nibble j of the result minus 8 is
+// signed digit j, in [-8, 7], and the carry out is digit 64 (0 or 1)
+__device__ __forceinline__ bool signed_nibbles(uint32_t (&u)[8]) {
+  uint64_t cy = 0;
+#pragma unroll
+  for (int k = 0; k < 8; k++) {
+    cy += uint64_t(u[k]) + 0x88888888u;
+    u[k] = uint32_t(cy);
+    cy >>= 32;
+  }
+  return cy != 0;
+}
+
+// A += d Q (d in [-8, 7]) from this lane's table
 template <class C>
-__device__ __forceinline__ XYZZ<C> vt_mul(const uint32_t* __restrict__ tab, uint32_t (&u)[8]) {
-  constexpr int SLOT = vt_slot<typename C::F>();
-  XYZZ<C> A = xyzz_inf<C>();
+__device__ __forceinline__ void vt_add_digit(Jz<C>& A, bool& inf, const uint32_t* __restrict__ tab, int d) {
+  using F = typename C::F;
+  if (d == 0) return;
+  const LzAffine<C> T = vt_get_affine<C>(tab + ((d < 0 ? -d : d) - 1) * vt_slot<F>());
+  if (T.x.w[0] >= 0) jz_madd<C>(A, inf, T.x, lz_neg_if<F>(T.y, d < 0));
+}
+
+// u Q from this lane's table (Q at tab): four doublings and one mixed
+// addition per signed digit from the most significant end; u (256 bits) is
+// consumed.  While the sum is O the doublings run on Q, unused.
+template <class C>
+__device__ __forceinline__ void vt_mul(Jz<C>& A, bool& inf, const uint32_t* __restrict__ tab, uint32_t (&u)[8]) {
+  using F = typename C::F;
+  inf = !signed_nibbles(u);
+  const LzAffine<C> Q = vt_get_affine<C>(tab);
+  A.X = Q.x;
+  A.Y = Q.y;
+  A.Z = lz_one<F>();
 #pragma unroll 1
   for (int w = 63; w >= 0; w--) {
-    if (w != 63) {
 #pragma unroll 1
-      for (int k = 0; k < 4; k++) A = xyzz_dbl_in<C>(A);
-    }
-    const uint32_t d = take_top<4>(u);
-    if (d != 0) A = xyzz_add_affine_in<C>(A, vt_get_affine<C>(tab + (d - 1) * SLOT));
+    for (int k = 0; k < 4; k++) jz_dbl<C>(A);
+    vt_add_digit<C>(A, inf, tab, int(take_top<4>(u)) - 8);
   }
-  return A;
+}
+
+// A += k G from the comb table, one mixed addition per byte of k (consumed)
+template <class C>
+__device__ __forceinline__ void comb_add(Xz<C>& A, bool& inf, const uint32_t* __restrict__ gcomb, uint32_t (&k)[8]) {
+  using F = typename C::F;
+  constexpr int PW = affine_words<C>();
+#pragma unroll 1
+  for (int j = 0; j < VCOMB_WINDOWS; j++) {
+    const uint32_t d = take_low<8>(k);
+    if (d != 0) {
+      const Affine<C> T = affine_load<C>(gcomb + size_t(j * VCOMB_ENTRIES + d) * PW);
+      xz_madd<C>(A, inf, lz_of<F>(T.x), lz_of<F>(T.y));
+    }
+  }
+}
+
+// The affine form (x, y) of a projective point, given lazily, at out as x then
+// y (N32 words each), plain or (out_mont) times R' = 2^(32 N32); O as zeros
+template <class C>
+__device__ __forceinline__ void store_lz_affine(const Lz<typename C::F>& x, const Lz<typename C::F>& y, bool inf,
+                                                bool active, uint32_t* __restrict__ out, int out_mont) {
+  using F = typename C::F;
+  constexpr int N32 = F::N32;
+  constexpr Words<F::NL> rout = F::ROUT;
+  Lz<F> k = lz_zero<F>();
+  k.w[0] = 1;
+  // Montgomery product with 1 leaves x; with R' = 2^(32 N32) leaves x R'
+  if (out_mont) k = lz_of<F>(fp_from<F>(rout));
+  uint32_t xw[N32], yw[N32];
+  fp_to_words<F>(lz_canonical<F>(lz_mul<F>(x, k)), xw);
+  fp_to_words<F>(lz_canonical<F>(lz_mul<F>(y, k)), yw);
+  if (inf) {
+#pragma unroll
+    for (int j = 0; j < N32; j++) xw[j] = yw[j] = 0;
+  }
+  if (active) {
+    words_store<F>(out, xw);
+    words_store<F>(out + N32, yw);
+  }
+}
+
+// X / ZZ = v for a canonical 256-bit v < p
+template <class C>
+__device__ __forceinline__ bool x_is(const Xz<C>& A, const uint32_t (&v)[8]) {
+  using F = typename C::F;
+  return lz_is_zero<F>(lz_sub<F>(lz_mul<F>(lz_of<F>(fp_to_mont<F>(fp_from_words<F>(v))), A.ZZ), A.X));
 }
 
 // scratch: VT_N * vt_slot<F>() words per lane of the grid (dead lanes included)
@@ -443,7 +535,6 @@ __global__ void __launch_bounds__(WG) k_verify_xyzz(const uint8_t* __restrict__ 
                                                     uint32_t* __restrict__ scratch, uint8_t* __restrict__ valid) {
   using F = typename C::F;
   using N = typename OrderField<C>::type;
-  constexpr int PW = affine_words<C>();
   __shared__ Fp<F> s_tot[WG / 64], s_inv[WG / 64];
   __shared__ Fp<N> n_tot[WG / 64], n_inv[WG / 64];
   const size_t i = size_t(blockIdx.x) * WG + threadIdx.x;
@@ -457,20 +548,23 @@ __global__ void __launch_bounds__(WG) k_verify_xyzz(const uint8_t* __restrict__ 
 
   uint32_t* tab = scratch + i * size_t(VT_N * vt_slot<F>());
   vt_build<C, WG>(tab, Q, s_tot, s_inv);
-  XYZZ<C> A = vt_mul<C>(tab, u2);  // A = u2 Q
-  // ---- A += u1 G ----
-#pragma unroll 1
-  for (int j = 0; j < VCOMB_WINDOWS; j++) {
-    const uint32_t d = take_low<8>(u1);
-    if (d != 0) A = xyzz_add_affine_in<C>(A, affine_load<C>(gcomb + size_t(j * VCOMB_ENTRIES + d) * PW));
+  Xz<C> A;
+  bool inf;
+  {  // A = u2 Q
+    Jz<C> J;
+    vt_mul<C>(J, inf, tab, u2);
+    A.X = J.X;
+    A.Y = J.Y;
+    A.ZZ = lz_sqr<F>(J.Z);
+    A.ZZZ = lz_mul<F>(J.Z, A.ZZ);
   }
+  comb_add<C>(A, inf, gcomb, u1);
 
   // ---- R.x mod n == r: R.x is below p < 2n, so R.x = r or R.x = r + n ----
   if (live) {
-    bool good = ok && !xyzz_is_inf<C>(A);
+    bool good = ok && !inf;
     if (good) {
-      const Fp<F> X = fp_canonical<F>(A.X);
-      bool eq = fp_eq_canonical<F>(X, fp_canonical<F>(fp_mul<F>(fp_to_mont<F>(fp_from_words<F>(rw)), A.ZZ)));
+      bool eq = x_is<C>(A, rw);
       uint32_t rn[8];
       uint64_t cy = 0;
 #pragma unroll
@@ -479,8 +573,7 @@ __global__ void __launch_bounds__(WG) k_verify_xyzz(const uint8_t* __restrict__ 
         rn[k] = uint32_t(v);
         cy = v >> 32;
       }
-      if (!eq && cy == 0 && words_lt8(rn, p32.w))
-        eq = fp_eq_canonical<F>(X, fp_canonical<F>(fp_mul<F>(fp_to_mont<F>(fp_from_words<F>(rn)), A.ZZ)));
+      if (!eq && cy == 0 && words_lt8(rn, p32.w)) eq = x_is<C>(A, rn);
       good = eq;
     }
     valid[i] = good ? 1 : 0;
@@ -503,7 +596,6 @@ __global__ void __launch_bounds__(WG) k_sign(const uint8_t* __restrict__ hashes,
                                              const uint32_t* __restrict__ gcomb, uint32_t* __restrict__ sigs) {
   using F = typename C::F;
   using N = typename OrderField<C>::type;
-  constexpr int PW = affine_words<C>();
   __shared__ Fp<F> s_tot[WG / 64], s_inv[WG / 64];
   __shared__ Fp<N> n_tot[WG / 64], n_inv[WG / 64];
   const size_t i = size_t(blockIdx.x) * WG + threadIdx.x;
@@ -532,16 +624,13 @@ __global__ void __launch_bounds__(WG) k_sign(const uint8_t* __restrict__ hashes,
   uint32_t kd[8];
 #pragma unroll
   for (int k = 0; k < 8; k++) kd[k] = kw[k];
-  XYZZ<C> A = xyzz_inf<C>();
-#pragma unroll 1
-  for (int j = 0; j < VCOMB_WINDOWS; j++) {
-    const uint32_t d = take_low<8>(kd);
-    if (d != 0) A = xyzz_add_affine_in<C>(A, affine_load<C>(gcomb + size_t(j * VCOMB_ENTRIES + d) * PW));
-  }
+  Xz<C> A;
+  bool inf = true;
+  comb_add<C>(A, inf, gcomb, kd);
   // 0 < k < n, so R != O and ZZ != 0
-  const Fp<F> izz = wg_batch_inverse<F, WG, 4>(A.ZZ, s_tot, s_inv);
+  const Fp<F> izz = wg_batch_inverse<F, WG, 4>(lz_semi<F>(A.ZZ), s_tot, s_inv);
   uint32_t rw[8];
-  fp_to_words<F>(fp_from_mont<F>(fp_canonical<F>(fp_mul<F>(A.X, izz))), rw);
+  fp_to_words<F>(fp_from_mont<F>(lz_semi<F>(lz_mul<F>(A.X, lz_of<F>(izz)))), rw);
   // r = R.x mod n: R.x < p < 2n
   if (!words_lt8(rw, n32.w)) {
     int64_t br = 0;
@@ -575,9 +664,9 @@ __global__ void __launch_bounds__(WG) k_sign(const uint8_t* __restrict__ hashes,
 //
 // out_i = k_i P_i for points known only at run time (the paper's UPMUL, the
 // unknown-point half of its batch PMUL workload, Section 3.4 and Table 5),
-// one request per lane: the table of d P_i and 4-bit windows of k_i as in
-// the per-lane verification, then the result's 1 / (ZZ ZZZ) by one GAS
-// inversion per workgroup.  pts are working-form affine points (the infinity
+// one request per lane: the table of d P_i and signed 4-bit windows of k_i as
+// in the per-lane verification, then the result's 1 / Z by one GAS inversion
+// per workgroup.  pts are working-form affine points (the infinity
 // marker for O); every k_i is a 256-bit integer, taken as is.
 template <class C, int WG>
 __global__ void __launch_bounds__(WG) k_pmul(const uint32_t* __restrict__ pts, const uint32_t* __restrict__ ks,
@@ -603,8 +692,14 @@ __global__ void __launch_bounds__(WG) k_pmul(const uint32_t* __restrict__ pts, c
   }
   uint32_t* tab = scratch + i * size_t(VT_N * vt_slot<F>());
   vt_build<C, WG>(tab, P, s_tot, s_inv);
-  const XYZZ<C> A = vt_mul<C>(tab, k);
-  store_xyzz_affine<C, WG>(A, pinf || xyzz_is_inf<C>(A), live, out + i * 2 * F::N32, out_mont, s_tot, s_inv);
+  Jz<C> A;
+  bool inf;
+  vt_mul<C>(A, inf, tab, k);
+  inf = inf || pinf;
+  const Lz<F> iz = lz_of<F>(wg_batch_inverse<F, WG>(inf ? fp_one<F>() : lz_semi<F>(A.Z), s_tot, s_inv));
+  const Lz<F> iz2 = lz_sqr<F>(iz);
+  store_lz_affine<C>(lz_mul<F>(A.X, iz2), lz_mul<F>(A.Y, lz_mul<F>(iz, iz2)), inf, live, out + i * 2 * F::N32,
+                     out_mont);
 }
 
 // ---- batched unknown-point multiplication in affine coordinates ------------
@@ -775,19 +870,19 @@ __global__ void __launch_bounds__(WG) k_fixed_base_comb(const uint32_t* __restri
                                                         const uint32_t* __restrict__ gcomb, uint32_t* __restrict__ out,
                                                         int out_mont) {
   using F = typename C::F;
-  constexpr int PW = affine_words<C>();
   __shared__ Fp<F> s_tot[WG / 64], s_inv[WG / 64];
   const size_t i = size_t(blockIdx.x) * WG + threadIdx.x;
   const bool active = i < n;
   uint32_t k[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   if (active) load_scalar(ks + 8 * i, k);
-  XYZZ<C> A = xyzz_inf<C>();
-#pragma unroll 1
-  for (int j = 0; j < VCOMB_WINDOWS; j++) {
-    const uint32_t d = take_low<8>(k);
-    if (d != 0) A = xyzz_add_affine_in<C>(A, affine_load<C>(gcomb + size_t(j * VCOMB_ENTRIES + d) * PW));
-  }
-  store_xyzz_affine<C, WG>(A, xyzz_is_inf<C>(A), active, out + i * 2 * F::N32, out_mont, s_tot, s_inv);
+  Xz<C> A;
+  bool inf = true;
+  comb_add<C>(A, inf, gcomb, k);
+  const Lz<F> one = lz_one<F>();
+  if (inf) xz_set<C>(A, one, one);
+  const Lz<F> t = lz_of<F>(wg_batch_inverse<F, WG>(lz_semi<F>(lz_mul<F>(A.ZZ, A.ZZZ)), s_tot, s_inv));
+  store_lz_affine<C>(lz_mul<F>(A.X, lz_mul<F>(t, A.ZZZ)), lz_mul<F>(A.Y, lz_mul<F>(t, A.ZZ)), inf, active,
+                     out + i * 2 * F::N32, out_mont);
 }
 
 }  // namespace eccmi
