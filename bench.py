@@ -35,6 +35,8 @@ PEAK_MAD32 = CUS * CLOCK_HZ * MAD32_PER_CU_CLK  # 3.93e13 /s
 # 2m^2 + m = 300 word multiply-adds each for m = 12 (381-bit field, D = 2^32)
 MAD32_PER_MUL = {1: 2 * 8 * 8 + 8, 2: 2 * 12 * 12 + 12}
 MULS_PER_AFFINE_ADD = 6
+# the accumulation kernel's own addition (mixed, XYZZ coordinates)
+MULS_PER_XYZZ_ADD = 10
 
 
 def adds_per_point(n: int, bits: int, c: int) -> float:
@@ -49,11 +51,11 @@ def algorithmic_mad32_per_point(n: int, bits: int, curve: int) -> float:
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bucket_round_traffic_bls12_381_n2p20.json")
-KERNEL_SOURCES = ["constants.h", "curves.h", "field.h", "inverse.h", "point.h", "kernels.h"]
+KERNEL_SOURCES = ["constants.h", "curves.h", "field.h", "inverse.h", "point.h", "kernels.h", "lazy.h", "accumulate.h"]
 
 
 def kernel_source_digest() -> str:
-    """sha256 over the device sources the bucket-round kernel is built from."""
+    """sha256 over the device sources the bucket-accumulation kernels are built from."""
     import hashlib
     h = hashlib.sha256()
     for name in KERNEL_SOURCES:
@@ -63,7 +65,7 @@ def kernel_source_digest() -> str:
 
 
 def measured_traffic():
-    """HBM bytes per bucket-round launch from the committed rocprofv3 counter
+    """HBM bytes per accumulation launch from the committed rocprofv3 counter
     summary (FETCH_SIZE and WRITE_SIZE scaled by a plain copy's readings), or
     None when the kernel sources changed since the counters were taken."""
     try:
@@ -684,17 +686,17 @@ def main() -> int:
           f"total {st['total_ms'] / args.steps:.3f}", file=sys.stderr, flush=True)
 
     value = n * args.steps / dt
-    per_add = MULS_PER_AFFINE_ADD * MAD32_PER_MUL[cid]
+    per_add = MULS_PER_XYZZ_ADD * MAD32_PER_MUL[cid]
     achieved = st["round_adds"] * per_add / (st["round_ms"] * 1e-3) if st["round_ms"] > 0 else 0.0
     roofline = {
         "bound": "alu",
-        "kernel": "k_bucket_round (batch-affine bucket accumulation)",
+        "kernel": "k_bucket_acc (bucket accumulation, mixed XYZZ additions)",
         "achieved": achieved / 1e12,
         "peak": PEAK_MAD32 / 1e12,
         "unit": "TOP/s",
         "frac": achieved / PEAK_MAD32,
         "traffic": measured_traffic(),
-        "per_unit": f"{per_add} MAD32 per batch-affine addition",
+        "per_unit": f"{per_add} MAD32 per mixed XYZZ addition",
         "units_per_launch": st["round_adds"] / max(1, st["round_launches"]),
         "avg_launch_ms": st["round_ms"] / max(1, st["round_launches"]),
         "finishing_pass_ms": st["finish_ms"] / args.steps,

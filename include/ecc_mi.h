@@ -121,23 +121,25 @@ size_t ecc_ctx_scratch_bytes(const ecc_ctx *ctx);
 typedef struct {
   uint64_t msm_calls;      /* ecc_msm calls measured */
   uint64_t points;         /* sum of n over those calls */
-  uint64_t round_launches; /* bucket-accumulation round kernels launched */
-  uint64_t round_adds;     /* batch-affine additions done by those kernels */
+  uint64_t round_launches; /* bucket-accumulation kernels launched (rounds, or one direct sum) */
+  uint64_t round_adds;     /* additions done by those kernels */
   double prepare_ms;       /* ingest, windowing, bucket grouping, schedule */
-  double round_ms;         /* bucket-accumulation rounds (sum of kernel times) */
+  double round_ms;         /* bucket accumulation (sum of those kernels' times) */
   double reduce_ms;        /* bucket reduction */
   double combine_ms;       /* window combination and output */
   double total_ms;         /* whole calls, first kernel to last */
-  double finish_ms;        /* per-lane finishing pass after the rounds (sum) */
+  double finish_ms;        /* finishing pass after the rounds, or the sums of cut buckets' parts */
 } ecc_stats;
 
 /* Turn per-phase timing on (1) or off (0); turning it on clears the stats. */
 ecc_status ecc_ctx_set_profiling(ecc_ctx *ctx, int enable);
 
-/* Design variant of the bucket-round kernel for later MSM calls on this
- * context, for ablations of the choices of Sections 3.2-3.4; every
- * variant gives the same results.  0 = the library's form (the default).
- * Bits 1-8 and 64 select a round kernel (BLS12-381 only): 1 stores each denominator
+/* Design variant of the bucket accumulation for later MSM calls on this
+ * context, for ablations of the choices of Sections 3.1-3.4; every
+ * variant gives the same results.  0 = the library's form (the default): each
+ * bucket's points are added on one lane, or a few, in XYZZ coordinates, with
+ * no inversion and no rounds.  Any other value runs the paper's batch-affine
+ * rounds.  Bits 1-8 and 64 select a round kernel (BLS12-381 only): 1 stores each denominator
  * in the compress step instead of recomputing it (Section 3.3 recomputes); 2
  * stores the prefix products per lane, contiguous, instead of limb-major
  * planes that coalesce across a wave; 4 splits the decompress step from the
@@ -145,10 +147,10 @@ ecc_status ecc_ctx_set_profiling(ecc_ctx *ctx, int enable);
  * every lane's chain product on its own lane instead of one GAS inversion
  * per workgroup (Section 3.2); 64 stores the prefix products of even steps
  * only and recomputes the odd ones (find-then-recompute, Section 3.4).  Bits
- * 16 and 32 choose where the rounds stop.
- * By default a single MSM stops them once they hold fewer additions than
+ * 16 and 32 choose where the rounds stop: unless bit 32 is set, those of a
+ * single MSM stop once they hold fewer additions than
  * twice the grid's lanes and no bucket has more than 16 partial sums, and
- * adds each bucket's remaining partial sums on its own lane in XYZZ
+ * each bucket's remaining partial sums are added on its own lane in XYZZ
  * coordinates, while a batch runs the rounds to the end; 16 takes the
  * finishing pass for batches too, 32 runs the rounds to the end for every
  * call (the paper's form).  Built round kernels: 1, 2, 3, 4, 7, 8, 64, each
@@ -168,8 +170,7 @@ ecc_status ecc_ctx_get_stats(const ecc_ctx *ctx, ecc_stats *out);
 ecc_status ecc_ctx_sync(ecc_ctx *ctx);
 
 /* Multi-scalar multiplication R = sum_{i < n} scalars_i * bases_i
- * (the plain definition; computed by Pippenger buckets with batch-affine
- * additions).
+ * (the plain definition; computed by Pippenger buckets).
  *   bases   : n points (2 L u64 each)        scalars : n x 4 u64
  *   out_xy  : 2 L u64                        out_inf : 1 byte
  * n = 0 gives the point at infinity.  Bases equal to (0, 0) contribute
@@ -184,10 +185,9 @@ ecc_status ecc_msm(ecc_ctx *ctx, ecc_curve curve, const uint64_t *bases, const u
 
 /* A batch of m independent MSMs in one launch sequence:
  *   R_j = sum over offsets[j] <= i < offsets[j+1] of scalars_i * bases_i.
- * The Pippenger buckets of all MSMs are accumulated together, so every round
- * of batch-affine additions (one Montgomery-trick chain per lane, one
- * Gather-Apply-Scatter inversion per workgroup, Sections 3.1-3.2) spans the
- * whole batch; reduction and window combination run per MSM.
+ * The Pippenger buckets of all MSMs are accumulated together in one launch
+ * (or, in a design variant, in rounds of batch-affine additions that span the
+ * whole batch); reduction and window combination run per MSM.
  *   bases, scalars : offsets[m] points and scalars, concatenated, laid out as
  *                    for ecc_msm (device pointers unless ECC_HOST_PTRS)
  *   offsets        : m + 1 u64 in HOST memory, offsets[0] = 0, non-decreasing

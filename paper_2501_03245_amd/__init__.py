@@ -41,7 +41,7 @@ ECC_BASES_PER_MSM = 1 << 8
 ECC_PMUL_BATCHED = 1 << 9
 ECC_PENDING = 1
 
-# design variants of the bucket-round kernel (ecc_ctx_set_round_variant)
+# design variants of the bucket accumulation (ecc_ctx_set_round_variant)
 RV_STORE_DENOM = 1
 RV_AOS_CHAIN = 2
 RV_SPLIT_APPLY = 4
@@ -266,7 +266,7 @@ class Context:
         return st.as_dict()
 
     def set_round_variant(self, variant: int) -> None:
-        """Design variant of the bucket-round kernel (ablations; 0 = library form)."""
+        """Design variant of the bucket accumulation (ablations; 0 = library form)."""
         self._check(_lib.ecc_ctx_set_round_variant(self._h, variant))
 
     def sync(self) -> None:

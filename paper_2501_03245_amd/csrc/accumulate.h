@@ -1,0 +1,400 @@
+// Bucket accumulation of the MSMs: every bucket's points, gathered from the
+// bases, are added on one lane (or several, for long buckets) in XYZZ
+// coordinates, and the reduction reads the sums in that form.
+//
+// What bounds it, and why not batch-affine rounds (Section 3): a batched
+// affine addition takes 6 products against the 10 (9 reductions) of a mixed
+// XYZZ one, but on this device the rounds spend most of their time elsewhere.
+// At BLS12-381 2^20 points (16.5 M additions) their products are 1.3 of
+// 3.2 ms at the measured product rate (74 10^9 /s); the rest is 734 B of
+// traffic per addition (two gathers of the point, prefix products, partial
+// sums), the inversion's latency and scans in each of five launches, and the
+// canonical forms that equality tests of stored points need.  Here an
+// addition reads its point once (128 B) and does nothing but its products:
+// the vector units are 90-94% busy in k_bucket_acc (3.0 10^13
+// lane-instructions/s, at the 2.0 GHz the clock settles to under them).
+// Measured, rounds and finishing pass before against accumulation and merge
+// now: BLS12-381 2^20 points 3.39 -> 2.60 ms (a call 4.55 -> 3.50 ms), 2^16
+// 0.74 -> 0.30 ms, 512 uneven MSMs 5.04 -> 3.75 ms, BN254 700001 points 1.77 ->
+// 0.95 ms (a call 2.56 -> 1.56 ms).
+//
+// Work items.  A bucket of n entries is cut into P = ceil(n / cap) nearly
+// equal parts, one lane each.  cap is 1.5 times the entries that each lane
+// of a full device (two waves on each SIMD) would get, and at least
+// ACC_MIN_CAP: large calls cut only the buckets that would outlast the rest
+// (a skewed window's), small ones cut every bucket, since a lane's additions
+// form a chain.  Items are ordered by length, longest first, by a counting
+// sort, so that the lanes of a wave end together (buckets of uniform scalars
+// hold 64 +- 8 entries at 2^20 points, and the longest of 64 lanes is 83) and
+// the last waves are short ones.  The partial sums of a cut bucket are added
+// by 1 to 16 lanes (a bucket has few parts, so lanes beyond that idle), or by a
+// workgroup when there are very many.
+#pragma once
+#include "kernels.h"
+#include "lazy.h"
+
+namespace eccmi {
+
+constexpr uint32_t ACC_BINS = 1024;       // item lengths told apart by the sort (longer ones share a bin)
+constexpr uint32_t ACC_MIN_CAP = 4;
+constexpr int ACC_MERGE_LG_LANES = 4;     // at most 16 lanes add the parts of a cut bucket
+constexpr uint32_t ACC_MERGE_TARGET = 65536;  // lanes the merge spreads over (one wave per SIMD)
+constexpr uint32_t ACC_MERGE_MAX = 256;   // parts beyond which a workgroup adds them
+constexpr int ACC_PLAN_WG = 1024;
+constexpr int ACC_WG = 256;
+constexpr int ACC_MERGE_WG = 256;
+
+// counters of one call, zeroed before it
+struct AccMeta {
+  uint32_t items;       // work items
+  uint32_t extra;       // parts beyond the first of their bucket
+  uint32_t cut;         // cut buckets of at most ACC_MERGE_MAX parts
+  uint32_t cut_big;     // cut buckets of more
+  uint32_t hist[ACC_BINS];  // items by bin
+  uint32_t cursor[ACC_BINS];
+};
+
+struct AccItem {
+  uint32_t first, len, slot, pad;  // entries [first, first + len) of the sorted list, summed into psum[slot]
+};
+
+struct AccCut {
+  uint32_t bucket, parts, extra;  // part 0 at psum[bucket], part j > 0 at psum[B + extra + j - 1]
+};
+
+struct AccLong {
+  uint32_t at, off, bucket, n, extra;
+};
+
+__host__ __device__ inline uint32_t acc_parts(uint32_t n, uint32_t cap) { return (n + cap - 1) / cap; }
+
+// bin of a bucket's parts: longest first
+__device__ __forceinline__ uint32_t acc_bin(uint32_t n, uint32_t parts) {
+  const uint32_t len = (n + parts - 1) / parts;
+  return ACC_BINS - 1 - (len < ACC_BINS ? len : ACC_BINS - 1);
+}
+
+// items per length
+static __global__ void __launch_bounds__(ACC_PLAN_WG) k_acc_count(const uint32_t* __restrict__ counts, uint32_t B,
+                                                                  uint32_t cap, AccMeta* __restrict__ meta) {
+  __shared__ uint32_t s_hist[ACC_BINS];
+  for (uint32_t i = threadIdx.x; i < ACC_BINS; i += ACC_PLAN_WG) s_hist[i] = 0;
+  __syncthreads();
+  for (uint32_t b = blockIdx.x * ACC_PLAN_WG + threadIdx.x; b < B; b += gridDim.x * ACC_PLAN_WG) {
+    const uint32_t n = counts[b];
+    if (n == 0) continue;
+    const uint32_t parts = acc_parts(n, cap);
+    atomicAdd(&s_hist[acc_bin(n, parts)], parts);
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < ACC_BINS; i += ACC_PLAN_WG)
+    if (s_hist[i]) atomicAdd(&meta->hist[i], s_hist[i]);
+}
+
+// the items in order of length, and the lists of cut buckets
+static __global__ void __launch_bounds__(ACC_PLAN_WG) k_acc_items(const uint32_t* __restrict__ counts,
+                                                                  const uint32_t* __restrict__ offsets, uint32_t B,
+                                                                  uint32_t cap, AccMeta* __restrict__ meta,
+                                                                  AccItem* __restrict__ items,
+                                                                  AccCut* __restrict__ cuts, uint32_t cut_cap) {
+  __shared__ uint32_t s_first[ACC_BINS], s_n[ACC_BINS], s_tmp[ACC_PLAN_WG / 64];
+  __shared__ uint32_t s_nlong;
+  __shared__ AccLong s_long[ACC_PLAN_WG];
+  static_assert(ACC_BINS == ACC_PLAN_WG, "one bin per thread");
+  const uint32_t t = threadIdx.x;
+  uint32_t total;
+  const uint32_t before = block_exclusive_scan<ACC_PLAN_WG>(meta->hist[t], s_tmp, total);
+  if (blockIdx.x == 0 && t == 0) meta->items = total;
+  const uint32_t b = blockIdx.x * ACC_PLAN_WG + t;
+  const uint32_t n = b < B ? counts[b] : 0u;
+  const uint32_t parts = acc_parts(n, cap);
+  const uint32_t bin = n ? acc_bin(n, parts) : 0u;
+  s_n[t] = 0;
+  if (t == 0) s_nlong = 0;
+  __syncthreads();
+  const uint32_t mine = n ? atomicAdd(&s_n[bin], parts) : 0u;
+  __syncthreads();
+  s_first[t] = before + (s_n[t] ? atomicAdd(&meta->cursor[t], s_n[t]) : 0u);
+  __syncthreads();
+  auto put = [&](uint32_t at, uint32_t off, uint32_t bucket, uint32_t entries, uint32_t np, uint32_t extra,
+                 uint32_t j) {
+    const uint32_t lo = uint32_t(uint64_t(entries) * j / np), hi = uint32_t(uint64_t(entries) * (j + 1) / np);
+    items[at + j] = AccItem{off + lo, hi - lo, j == 0 ? bucket : B + extra + j - 1, 0u};
+  };
+  if (n != 0) {
+    const uint32_t at = s_first[bin] + mine, off = offsets[b];
+    uint32_t extra = 0;
+    if (parts > 1) {
+      extra = atomicAdd(&meta->extra, parts - 1);
+      if (parts <= ACC_MERGE_MAX) cuts[atomicAdd(&meta->cut, 1u)] = AccCut{b, parts, extra};
+      else cuts[cut_cap - 1 - atomicAdd(&meta->cut_big, 1u)] = AccCut{b, parts, extra};
+    }
+    if (parts <= 64) {
+      for (uint32_t j = 0; j < parts; j++) put(at, off, b, n, parts, extra, j);
+    } else {
+      s_long[atomicAdd(&s_nlong, 1u)] = AccLong{at, off, b, n, extra};  // one slot per thread at most
+    }
+  }
+  __syncthreads();
+  // the items of a bucket of many parts (a skewed window's) by the whole workgroup
+  const uint32_t nlong = s_nlong;
+  for (uint32_t q = 0; q < nlong; q++) {
+    const AccLong g = s_long[q];
+    const uint32_t np = acc_parts(g.n, cap);
+    for (uint32_t j = t; j < np; j += ACC_PLAN_WG) put(g.at, g.off, g.bucket, g.n, np, g.extra, j);
+  }
+}
+
+// One item per lane: its entries added in XYZZ coordinates (madd-2008-s, see
+// xz_madd).  The next point is loaded into the registers of the current one
+// as soon as its two products are done, so its latency passes behind the
+// other seven; the sorted words run two entries ahead.
+template <class C>
+__global__ void __launch_bounds__(ACC_WG) __attribute__((amdgpu_waves_per_eu(2))) k_bucket_acc(
+    const uint32_t* __restrict__ bases, const uint32_t* __restrict__ sorted, const AccMeta* __restrict__ meta,
+    const AccItem* __restrict__ items, uint32_t* __restrict__ psum) {
+  using F = typename C::F;
+  constexpr int PW = affine_words<C>();
+  const uint32_t i = blockIdx.x * ACC_WG + threadIdx.x;
+  if (i >= meta->items) return;
+  const AccItem it = items[i];
+  const uint32_t* src = sorted + it.first;
+  uint32_t s1 = src[0], s2 = it.len > 1 ? src[1] : 0u;
+  Lz<F> bx = lz_load<F>(bases + size_t(s1 & ~SIGN_BIT) * PW);
+  Lz<F> by = lz_neg_if<F>(lz_load<F>(bases + size_t(s1 & ~SIGN_BIT) * PW + F::CW), (s1 & SIGN_BIT) != 0);
+  Xz<C> A;
+  bool inf = true;
+#pragma unroll 1
+  for (uint32_t k = 0; k < it.len; k++) {
+    bool add = !inf;
+    Lz<F> P, R;
+    if (inf) {
+      xz_set<C>(A, bx, by);
+      inf = false;
+    } else {
+      lz_pair<F>(ColMul<F>{bx, A.ZZ}, ColMul<F>{by, A.ZZZ}, P, R);
+      P = lz_sub<F>(P, A.X);
+      R = lz_sub<F>(R, A.Y);
+      if (lz_maybe_zero<F, 8>(P)) {
+        if (lz_is_zero<F>(P)) {
+          if (lz_is_zero<F>(R)) xz_mdbl<C>(A, bx, by);
+          else inf = true;
+          add = false;
+        }
+      }
+    }
+    if (k + 1 < it.len) {
+      const uint32_t s = s2;
+      if (k + 2 < it.len) s2 = src[k + 2];
+      const uint32_t* p = bases + size_t(s & ~SIGN_BIT) * PW;
+      bx = lz_load<F>(p);
+      by = lz_load<F>(p + F::CW);
+      s1 = s;
+    }
+    if (add) xz_madd_tail<C>(A, P, R);
+    by = lz_neg_if<F>(by, (s1 & SIGN_BIT) != 0);
+  }
+  xz_store<C>(psum + size_t(it.slot) * xyzz_words<C>(), A, inf);
+}
+
+// the partial sums of a cut bucket: lane l of G adds the parts l, l + G, ...,
+// then a tree over the lanes (one addition in the code for both); the sum goes
+// back to part 0's place.  All 64 lanes of the wave stay in step.
+template <class C>
+__device__ __forceinline__ void acc_merge(Xz<C>& A, bool& inf, const AccCut& cut, uint32_t l, uint32_t G, uint32_t B,
+                                          const uint32_t* __restrict__ psum, int tree) {
+  constexpr int XW = xyzz_words<C>();
+  const uint32_t mine = l < cut.parts ? (cut.parts - l + G - 1) / G : 0u;
+  uint32_t most = mine;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) most = max(most, uint32_t(__shfl_xor(int(most), d, 64)));
+  inf = true;
+  const uint32_t steps = most + uint32_t(tree);
+#pragma unroll 1
+  for (uint32_t st = 0; st < steps; st++) {
+    Xz<C> Bp;
+    bool binf = true;
+    if (st < most) {
+      if (st < mine) {
+        const uint32_t j = l + st * G;
+        xz_load<C>(psum + size_t(j == 0 ? cut.bucket : B + cut.extra + j - 1) * XW, Bp, binf);
+      }
+    } else {
+      const int off = 1 << (tree - 1 - int(st - most));
+      xz_map<C>(Bp, A, [&](int32_t v) { return __shfl_down(v, off, 64); });
+      binf = __shfl_down(int(inf), off, 64) != 0 || (l & 63u) + uint32_t(off) >= min(G, 64u);
+    }
+    xz_add<C>(A, inf, Bp, binf);
+  }
+}
+
+template <class C>
+__global__ void __launch_bounds__(ACC_MERGE_WG) __attribute__((amdgpu_waves_per_eu(2, 2))) k_acc_merge(
+    const AccMeta* __restrict__ meta, const AccCut* __restrict__ cuts, uint32_t B, uint32_t* __restrict__ psum) {
+  const uint32_t n = meta->cut;
+  if (n == 0) return;
+  // lanes per bucket: as many as leave one wave on each SIMD, since a lane's
+  // additions form a chain; one lane each where there are buckets enough
+  int lgG = 0;
+  while (lgG < ACC_MERGE_LG_LANES && (n << (lgG + 1)) <= ACC_MERGE_TARGET) lgG++;
+  const uint32_t G = 1u << lgG;
+  const uint32_t l = threadIdx.x & (G - 1);
+  // the wave's cut buckets; the loop's bounds are wave-uniform
+  for (uint32_t w = (blockIdx.x * ACC_MERGE_WG + threadIdx.x) / 64; (w << (6 - lgG)) < n;
+       w += gridDim.x * (ACC_MERGE_WG / 64)) {
+    const uint32_t i = (w << (6 - lgG)) + ((threadIdx.x & 63u) >> lgG);
+    const AccCut cut = i < n ? cuts[i] : AccCut{0u, 0u, 0u};
+    int tree = 0;  // levels the widest of the wave's buckets needs
+    while (tree < lgG && __ballot((1u << tree) < cut.parts) != 0) tree++;
+    Xz<C> A;
+    bool inf;
+    acc_merge<C>(A, inf, cut, l, G, B, psum, tree);
+    if (i < n && l == 0) xz_store<C>(psum + size_t(cut.bucket) * xyzz_words<C>(), A, inf);
+  }
+}
+
+template <class C>
+__global__ void __launch_bounds__(ACC_MERGE_WG) __attribute__((amdgpu_waves_per_eu(2, 2))) k_acc_merge_big(
+    const AccMeta* __restrict__ meta, const AccCut* __restrict__ cuts, uint32_t cut_cap, uint32_t B,
+    uint32_t* __restrict__ psum) {
+  constexpr int NW = ACC_MERGE_WG / 64;
+  __shared__ uint32_t s_pt[NW][xyzz_words<C>()];
+  const uint32_t n = meta->cut_big;
+  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const AccCut cut = cuts[cut_cap - 1 - i];
+    Xz<C> A;
+    bool inf;
+    acc_merge<C>(A, inf, cut, threadIdx.x, ACC_MERGE_WG, B, psum, 6);
+    if ((threadIdx.x & 63u) == 0) xz_store<C>(s_pt[threadIdx.x / 64], A, inf);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll 1
+      for (int w = 1; w < NW; w++) {
+        Xz<C> Bp;
+        bool binf;
+        xz_load<C>(s_pt[w], Bp, binf);
+        xz_add<C>(A, inf, Bp, binf);
+      }
+      xz_store<C>(psum + size_t(cut.bucket) * xyzz_words<C>(), A, inf);
+    }
+    __syncthreads();
+  }
+}
+
+// ---- bucket reduction, level A, over the sums above ---------------------------
+// The scheme of k_reduce_a (kernels.h) on lazy limbs.
+
+// seg_weighted_sum for lazy points; t_inf: T_t is O
+template <class C, class GetT, class PutU>
+__device__ __forceinline__ void xz_seg_weighted_sum(Xz<C>& a, bool& inf, int lgS, int lgM, GetT get_T, PutU put_U) {
+  const int lane = threadIdx.x & 63;
+  const int seg = 1 << lgS;
+  const int t = lane & (seg - 1);
+  const int nsteps = lgS + lgM + 1 + lgS;
+#pragma unroll 1
+  for (int st = 0; st < nsteps; st++) {
+    if (st == lgS && t == 0) put_U(a, inf);  // the segment total, after the scan
+    if (st >= lgS && st < lgS + lgM) {
+      if (!inf) xz_dbl<C>(a);
+      continue;
+    }
+    Xz<C> b;
+    bool binf;
+    if (st < lgS) {
+      const int off = 1 << st;
+      xz_map<C>(b, a, [&](int32_t v) { return __shfl_down(v, off, 64); });
+      binf = __shfl_down(int(inf), off, 64) != 0 || t + off >= seg;
+    } else if (st == lgS + lgM) {
+      inf = inf || t < 1;
+      get_T(b, binf);
+    } else {
+      const int m = seg >> (st - lgS - lgM);
+      xz_map<C>(b, a, [&](int32_t v) { return __shfl_xor(v, m, 64); });
+      binf = __shfl_xor(int(inf), m, 64) != 0;
+    }
+    xz_add<C>(a, inf, b, binf);
+  }
+}
+
+template <class C, int WG>
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2))) k_reduce_a_xz(
+    const uint32_t* __restrict__ counts, const uint32_t* __restrict__ psum, const RedJob* __restrict__ jobs,
+    const RedWave* __restrict__ waves, uint32_t nwaves, uint32_t* __restrict__ segU, uint32_t* __restrict__ segY,
+    uint32_t* __restrict__ winsum) {
+  constexpr int XW = xyzz_words<C>();
+  constexpr int NL = C::F::NL;
+  const uint32_t gw = (blockIdx.x * WG + threadIdx.x) >> 6;  // uniform per wave
+  if (gw >= nwaves) return;
+  const uint32_t lane = threadIdx.x & 63;
+  const RedWave wv = waves[gw];
+  const int lgS = int(wv.lgS);
+  const uint32_t slot = lane >> lgS;             // job slot inside the wave
+  const uint32_t t = lane & ((1u << lgS) - 1u);  // lane inside the segment
+  const bool active = slot < wv.njobs;
+  const RedJob jb = jobs[wv.job + (active ? slot : 0u)];
+  const int lgLam = int(jb.lgLam);
+  const int lgL = int(jb.lgD) - lgLam;
+  const uint32_t L = 1u << lgL;
+  const uint32_t first = jb.bucket + ((wv.g << 6) + t) * L;  // L buckets from here
+  // T lives in LDS (one word per limb and thread, touched by its own thread
+  // only): the registers hold one addition's two operands
+  __shared__ int32_t s_T[4 * NL * WG];
+  int32_t* const sT = s_T + threadIdx.x;
+  auto load_T = [&](Xz<C>& P) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NL; i++) {
+      P.X.w[i] = sT[(0 * NL + i) * WG];
+      P.Y.w[i] = sT[(1 * NL + i) * WG];
+      P.ZZ.w[i] = sT[(2 * NL + i) * WG];
+      P.ZZZ.w[i] = sT[(3 * NL + i) * WG];
+    }
+  };
+  Xz<C> S;
+  bool sinf = true, tinf = true;
+  // S += B_k, then T += S: one addition in the code
+#pragma unroll 1
+  for (uint32_t st = 0; st < 2 * L; st++) {
+    Xz<C> Bz;
+    bool binf = true;
+    const bool second = st & 1u;
+    if (second) {
+      Bz = S;
+      binf = sinf;
+      load_T(S);
+      sinf = tinf;
+    } else if (active) {
+      const uint32_t b = first + L - 1 - st / 2;
+      if (counts[b]) xz_load<C>(psum + size_t(b) * XW, Bz, binf);
+    }
+    xz_add<C>(S, sinf, Bz, binf);
+    if (second) {
+#pragma unroll
+      for (int i = 0; i < NL; i++) {
+        sT[(0 * NL + i) * WG] = S.X.w[i];
+        sT[(1 * NL + i) * WG] = S.Y.w[i];
+        sT[(2 * NL + i) * WG] = S.ZZ.w[i];
+        sT[(3 * NL + i) * WG] = S.ZZZ.w[i];
+      }
+      tinf = sinf;
+      S = Bz;
+      sinf = binf;
+    }
+  }
+  const bool big = lgLam > 6;
+  xz_seg_weighted_sum<C>(
+      S, sinf, lgS, lgL,
+      [&](Xz<C>& b, bool& binf) {
+        load_T(b);
+        binf = tinf;
+      },
+      [&](const Xz<C>& U, bool uinf) {
+        if (active && big) xyzz_store<C>(segU + size_t(jb.seg_base + wv.g) * XW, xz_to_xyzz<C>(U, uinf));
+      });
+  if (active && t == 0) {
+    const XYZZ<C> Y = xz_to_xyzz<C>(S, sinf);
+    if (!big) xyzz_store<C>(winsum + size_t(wv.job + slot) * XW, Y);
+    else xyzz_store<C>(segY + size_t(jb.seg_base + wv.g) * XW, Y);
+  }
+}
+
+}  // namespace eccmi

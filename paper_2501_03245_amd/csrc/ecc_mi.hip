@@ -391,10 +391,24 @@ ecc_status enqueue_radix_sort(ecc_ctx* ctx, const SortGeom& s, const uint32_t* d
 }
 
 // whether the rounds of a call of m MSMs may hand over to the finishing pass
-// (single MSMs by default; batches too with RV_FINISH; never with RV_ROUNDS_ONLY)
+// (single MSMs unless RV_ROUNDS_ONLY; batches with RV_FINISH)
 bool finish_enabled(const ecc_ctx* ctx, size_t m) {
   return (ctx->round_variant & RV_FINISH) || (m == 1 && !(ctx->round_variant & RV_ROUNDS_ONLY));
 }
+
+// Whether a call sums its buckets directly (accumulate.h); a design variant of
+// the rounds runs the batch-affine rounds instead.
+bool direct_sums(const ecc_ctx* ctx) { return ctx->round_variant == 0; }
+
+// entries per work item of the direct sums, from the bound on all entries
+uint32_t acc_cap(const ecc_ctx* ctx, size_t E) {
+  const size_t lanes = size_t(ctx->cu_count) * 4 * 64 * 2;  // two waves on each SIMD
+  return std::max(ACC_MIN_CAP, uint32_t((E + E / 2 + lanes - 1) / lanes));
+}
+
+// bound on the parts of cut buckets beyond their first (a bucket of n entries
+// has at most n / cap of them), and so on the number of cut buckets
+size_t acc_extra(const ecc_ctx* ctx, size_t E) { return E / acc_cap(ctx, E) + 1; }
 
 // Scratch for a geometry (all device buffers of the context).
 template <class C>
@@ -402,7 +416,7 @@ ecc_status reserve_msm(ecc_ctx* ctx, const Geometry& g, uint32_t lanes_max) {
   constexpr int NL = C::F::NL;
   constexpr int PW = affine_words<C>();
   constexpr int XW = xyzz_words<C>();
-  size_t adds_max = g.E / 2 + 1;
+  const size_t adds_max = g.E / 2 + 1;
   ECC_TRY(ensure(ctx, ctx->bases, (g.glv || g.glv_batch ? 2 : 1) * g.n * PW * 4));
   ECC_TRY(ensure(ctx, ctx->skip, (g.glv_batch ? 2 : 1) * g.n));
   if (g.glv_batch) ECC_TRY(ensure(ctx, ctx->hscal, 2 * g.n * 32));
@@ -410,23 +424,172 @@ ecc_status reserve_msm(ecc_ctx* ctx, const Geometry& g, uint32_t lanes_max) {
   ECC_TRY(ensure(ctx, ctx->offsets, (g.B + 1) * 4));
   ECC_TRY(ensure(ctx, ctx->cursor, g.B * 4));
   ECC_TRY(ensure(ctx, ctx->sorted, g.E * 4));
-  ECC_TRY(ensure(ctx, ctx->slots, g.slot_cap * PW * 4));
-  ECC_TRY(ensure(ctx, ctx->slots2, g.slot_cap * PW * 4));
-  ECC_TRY(ensure(ctx, ctx->desc, g.desc_total * 8));
-  ECC_TRY(ensure(ctx, ctx->tails, g.tail_total * 8));
-  // prefix products (and, for the stored-denominator variant, the denominators
-  // in a second area of the same size)
-  const size_t chain_words = (adds_max + lanes_max + ROUND_WG) * NL;
-  ECC_TRY(ensure(ctx, ctx->mscr, ((ctx->round_variant & RV_STORE_DENOM) ? 2 : 1) * chain_words * 4));
+  if (direct_sums(ctx)) {
+    const size_t extra = acc_extra(ctx, g.E);
+    ECC_TRY(ensure(ctx, ctx->psum, (g.B + extra) * XW * 4));
+    ECC_TRY(ensure(ctx, ctx->aitems, (std::min(g.B, g.E) + extra) * sizeof(AccItem)));
+    ECC_TRY(ensure(ctx, ctx->acuts, extra * sizeof(AccCut)));
+    ECC_TRY(ensure(ctx, ctx->ameta, sizeof(AccMeta)));
+  } else {
+    ECC_TRY(ensure(ctx, ctx->slots, g.slot_cap * PW * 4));
+    ECC_TRY(ensure(ctx, ctx->slots2, g.slot_cap * PW * 4));
+    ECC_TRY(ensure(ctx, ctx->desc, g.desc_total * 8));
+    ECC_TRY(ensure(ctx, ctx->tails, g.tail_total * 8));
+    // prefix products (and, for the stored-denominator variant, the denominators
+    // in a second area of the same size)
+    const size_t chain_words = (adds_max + lanes_max + ROUND_WG) * NL;
+    ECC_TRY(ensure(ctx, ctx->mscr, ((ctx->round_variant & RV_STORE_DENOM) ? 2 : 1) * chain_words * 4));
+    if (finish_enabled(ctx, g.msms.size())) ECC_TRY(ensure(ctx, ctx->fzz, g.B * 2 * C::F::CW * 4));
+  }
   ECC_TRY(ensure(ctx, ctx->segS, size_t(g.nseg) * XW * 4));
   ECC_TRY(ensure(ctx, ctx->segT, size_t(g.nseg) * XW * 4));
   ECC_TRY(ensure(ctx, ctx->winsum, g.jobs.size() * XW * 4));
   ECC_TRY(ensure(ctx, ctx->flags, (2 + 2 * MAX_ROUNDS) * 4));
   ECC_TRY(ensure(ctx, ctx->rparams, (MAX_ROUNDS + 1) * sizeof(uint4)));
   ECC_TRY(ensure(ctx, ctx->scan_tmp, scan_tmp_words(g.B + 1) * 4));
-  if (finish_enabled(ctx, g.msms.size())) ECC_TRY(ensure(ctx, ctx->fzz, g.B * 2 * C::F::CW * 4));
   SortGeom sg;
   if (sort_geometry(g, sg)) ECC_TRY(reserve_radix_sort(ctx, sg));
+  return ECC_OK;
+}
+
+// The direct sums of every bucket and level A of their reduction (counts,
+// offsets and sorted entries are made).  *nr and *finished as for the rounds:
+// one accumulation launch, and whether cut buckets may have been merged.
+template <class C>
+ecc_status enqueue_direct(ecc_ctx* ctx, const Geometry& g, hipStream_t st, bool prof, int* nr, bool* finished) {
+  *nr = 0;
+  *finished = false;
+  const uint32_t B = uint32_t(g.B);
+  AccMeta* meta = P<AccMeta>(ctx->ameta);
+  uint32_t* counts = P<uint32_t>(ctx->counts);
+  uint32_t* psum = P<uint32_t>(ctx->psum);
+  const uint32_t cap = acc_cap(ctx, g.E);
+  const size_t extra = acc_extra(ctx, g.E);
+  if (B) {
+    ECC_TRY(fill_u32(ctx, P<uint32_t>(ctx->ameta), sizeof(AccMeta) / 4, 0u, st));
+    k_acc_count<<<std::min<uint32_t>(ceil_div(B, ACC_PLAN_WG), uint32_t(ctx->cu_count)), ACC_PLAN_WG, 0, st>>>(
+        counts, B, cap, meta);
+    HIP_TRY(hipGetLastError());
+    k_acc_items<<<ceil_div(B, ACC_PLAN_WG), ACC_PLAN_WG, 0, st>>>(counts, P<uint32_t>(ctx->offsets), B, cap, meta,
+                                                                  P<AccItem>(ctx->aitems), P<AccCut>(ctx->acuts),
+                                                                  uint32_t(extra));
+    HIP_TRY(hipGetLastError());
+  }
+  if (prof) ECC_TRY(record(ctx, 1, st));
+  if (!B) return ECC_OK;
+  if (prof) ECC_TRY(record(ctx, 2, st));
+  k_bucket_acc<C><<<ceil_div(std::min(g.B, g.E) + extra, ACC_WG), ACC_WG, 0, st>>>(
+      P<uint32_t>(ctx->bases), P<uint32_t>(ctx->sorted), meta, P<AccItem>(ctx->aitems), psum);
+  HIP_TRY(hipGetLastError());
+  if (prof) ECC_TRY(record(ctx, 3, st));
+  *nr = 1;
+  if (g.max_n > cap) {  // no bucket holds more entries than its MSM has points
+    if (prof) ECC_TRY(record(ctx, 4, st));
+    const uint32_t blocks = std::min<uint32_t>(ceil_div(extra << ACC_MERGE_LG_LANES, ACC_MERGE_WG), 1024u);
+    k_acc_merge<C><<<blocks, ACC_MERGE_WG, 0, st>>>(meta, P<AccCut>(ctx->acuts), B, psum);
+    HIP_TRY(hipGetLastError());
+    if (g.max_n > uint64_t(cap) * ACC_MERGE_MAX) {
+      k_acc_merge_big<C><<<256, ACC_MERGE_WG, 0, st>>>(meta, P<AccCut>(ctx->acuts), uint32_t(extra), B, psum);
+      HIP_TRY(hipGetLastError());
+    }
+    if (prof) ECC_TRY(record(ctx, 5, st));
+    *finished = true;
+  }
+  k_reduce_a_xz<C, REDUCE_WG><<<unsigned(ceil_div(g.waves.size() * 64, REDUCE_WG)), REDUCE_WG, 0, st>>>(
+      counts, psum, GP<RedJob>(ctx, g.off_jobs), GP<RedWave>(ctx, g.off_waves), uint32_t(g.waves.size()),
+      P<uint32_t>(ctx->segS), P<uint32_t>(ctx->segT), P<uint32_t>(ctx->winsum));
+  HIP_TRY(hipGetLastError());
+  return ECC_OK;
+}
+
+// The batch-affine rounds of a design variant, the finishing pass where it
+// runs, and level A of the reduction.
+template <class C>
+ecc_status enqueue_rounds(ecc_ctx* ctx, const Geometry& g, hipStream_t st, uint32_t lanes_max, bool exact_rounds,
+                          int* rounds_run, uint64_t* adds_run, bool* finished) {
+  uint32_t* d_flags = P<uint32_t>(ctx->flags);
+  uint32_t* d_maxn = d_flags + 1 + 2 * MAX_ROUNDS;
+  const bool prof = exact_rounds && ctx->profiling;
+  if (g.B) {
+    k_plan<PLAN_WG><<<ceil_div(g.B, PLAN_WG), PLAN_WG, 0, st>>>(
+        P<uint32_t>(ctx->counts), P<uint32_t>(ctx->offsets), uint32_t(g.B), P<uint2>(ctx->desc),
+        GP<size_t>(ctx, g.off_desc_base), P<uint2>(ctx->tails), GP<size_t>(ctx, g.off_tail_base), d_flags + 1,
+        d_flags + 1 + MAX_ROUNDS, d_maxn);
+    HIP_TRY(hipGetLastError());
+  }
+  const uint32_t lmax = finish_enabled(ctx, g.msms.size()) ? ctx->fin_lmax : 0u;
+  k_round_params<<<1, 64, 0, st>>>(d_flags + 1, lanes_max, ROUND_WG, g.kmin, P<uint4>(ctx->rparams), d_maxn, lmax);
+  HIP_TRY(hipGetLastError());
+  if (prof) ECC_TRY(record(ctx, 1, st));
+
+  uint32_t counts[MAX_ROUNDS], tails[MAX_ROUNDS];
+  // rounds launched (eager: those with work, up to the hand-over to the
+  // finishing pass; graph: the bound, each reading its own parameters)
+  int nr = g.B ? std::max(1, g.rounds) : 0;
+  bool finish = g.B != 0 && !exact_rounds && lmax != 0;
+  uint64_t adds = 0;
+  if (exact_rounds) {
+    HIP_TRY(hipMemcpyAsync(ctx->host_small, d_flags, (2 + 2 * MAX_ROUNDS) * 4, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    memcpy(counts, ctx->host_small + 1, sizeof(counts));
+    memcpy(tails, ctx->host_small + 1 + MAX_ROUNDS, sizeof(tails));
+    int with_work = 0;
+    while (with_work < MAX_ROUNDS && (counts[with_work] || tails[with_work])) with_work++;
+    nr = int(finish_round(counts, ctx->host_small[1 + 2 * MAX_ROUNDS], uint32_t(with_work), lmax, 2 * lanes_max));
+    finish = nr < with_work;
+    for (int r = 0; r < nr; r++) adds += counts[r];  // the batch-affine additions of the rounds run
+  }
+  const Planes<C> A = planes<C>(ctx->slots, g.slot_cap), Bp = planes<C>(ctx->slots2, g.slot_cap);
+  for (int r = 0; r < nr; r++) {
+    const Planes<C>& out = (r & 1) ? Bp : A;
+    const Planes<C>& in = (r & 1) ? A : Bp;  // the previous round's output (unused in round 0)
+    if (prof) ECC_TRY(record(ctx, 2 + 2 * r, st));
+    uint32_t blocks = lanes_max / ROUND_WG;
+    if (exact_rounds) blocks = round_lane_count(counts[r], lanes_max, ROUND_WG, g.kmin) / ROUND_WG;
+    if (ctx->round_variant & RV_KERNEL_MASK) {
+      const size_t chain_words = (g.E / 2 + 1 + lanes_max + ROUND_WG) * C::F::NL;
+      HIP_TRY(launch_round_variant_bls(ctx->round_variant & RV_KERNEL_MASK, blocks, st, P<uint32_t>(ctx->bases),
+                                       P<uint32_t>(ctx->sorted), in.x, in.y, out.x, out.y,
+                                       P<uint2>(ctx->desc) + g.desc_base[r], P<uint4>(ctx->rparams) + r,
+                                       r == 0 ? 1 : 0, P<uint32_t>(ctx->mscr), P<uint2>(ctx->tails) + g.tail_base[r],
+                                       d_flags + 1 + MAX_ROUNDS + r, P<uint32_t>(ctx->mscr) + chain_words));
+    } else {
+      launch_round<C>(g.occ, blocks, st, P<uint32_t>(ctx->bases), P<uint32_t>(ctx->sorted), in.x, in.y, out.x,
+                      out.y, P<uint2>(ctx->desc) + g.desc_base[r], P<uint4>(ctx->rparams) + r, r == 0 ? 1 : 0,
+                      P<uint32_t>(ctx->mscr), P<uint2>(ctx->tails) + g.tail_base[r], d_flags + 1 + MAX_ROUNDS + r);
+      HIP_TRY(hipGetLastError());
+    }
+    if (prof) ECC_TRY(record(ctx, 3 + 2 * r, st));
+  }
+  if (finish) {
+    // the rounds left out: each bucket's remaining partial sums on its own lane
+    if (prof) ECC_TRY(record(ctx, 2 + 2 * nr, st));
+    k_bucket_finish<C, FINISH_WG><<<ceil_div(g.B, FINISH_WG), FINISH_WG, 0, st>>>(
+        P<uint32_t>(ctx->counts), P<uint32_t>(ctx->offsets), uint32_t(g.B), A.x, A.y, Bp.x, Bp.y,
+        P<uint32_t>(ctx->fzz), P<uint4>(ctx->rparams) + MAX_ROUNDS);
+    HIP_TRY(hipGetLastError());
+    if (prof) ECC_TRY(record(ctx, 3 + 2 * nr, st));
+  }
+  if (g.waves.size()) {
+    // bucket sums in XYZZ form where the finishing pass ran (or, in a graph,
+    // may run: then the reduction reads from the device whether it did)
+    const unsigned blocks = unsigned(ceil_div(g.waves.size() * 64, REDUCE_WG));
+    if (finish) {
+      k_reduce_a<C, REDUCE_WG, true><<<blocks, REDUCE_WG, 0, st>>>(
+          P<uint32_t>(ctx->counts), P<uint32_t>(ctx->offsets), A.x, A.y, Bp.x, Bp.y, GP<RedJob>(ctx, g.off_jobs),
+          GP<RedWave>(ctx, g.off_waves), uint32_t(g.waves.size()), P<uint32_t>(ctx->segS), P<uint32_t>(ctx->segT),
+          P<uint32_t>(ctx->winsum), P<uint32_t>(ctx->fzz), P<uint4>(ctx->rparams) + MAX_ROUNDS);
+    } else {
+      k_reduce_a<C, REDUCE_WG><<<blocks, REDUCE_WG, 0, st>>>(
+          P<uint32_t>(ctx->counts), P<uint32_t>(ctx->offsets), A.x, A.y, Bp.x, Bp.y, GP<RedJob>(ctx, g.off_jobs),
+          GP<RedWave>(ctx, g.off_waves), uint32_t(g.waves.size()), P<uint32_t>(ctx->segS), P<uint32_t>(ctx->segT),
+          P<uint32_t>(ctx->winsum));
+    }
+    HIP_TRY(hipGetLastError());
+  }
+  *rounds_run = nr;
+  *adds_run = adds;
+  *finished = finish;
   return ECC_OK;
 }
 
@@ -446,7 +609,6 @@ ecc_status enqueue_msm(ecc_ctx* ctx, const Geometry& g, const uint32_t* d_bases_
   // flags: [0] error bits, [1 + r] additions of round r, [1 + MAX_ROUNDS + r] tail copies of round r,
   // [1 + 2 MAX_ROUNDS] the largest bucket
   uint32_t* d_flags = P<uint32_t>(ctx->flags);
-  uint32_t* d_maxn = d_flags + 1 + 2 * MAX_ROUNDS;
   const bool prof = exact_rounds && ctx->profiling;
   SortGeom sg;
   const bool radix = sort_geometry(g, sg);
@@ -517,82 +679,13 @@ ecc_status enqueue_msm(ecc_ctx* ctx, const Geometry& g, const uint32_t* d_bases_
       HIP_TRY(hipGetLastError());
     }
   }
-  if (g.B) {
-    k_plan<PLAN_WG><<<ceil_div(g.B, PLAN_WG), PLAN_WG, 0, st>>>(
-        P<uint32_t>(ctx->counts), P<uint32_t>(ctx->offsets), uint32_t(g.B), P<uint2>(ctx->desc),
-        GP<size_t>(ctx, g.off_desc_base), P<uint2>(ctx->tails), GP<size_t>(ctx, g.off_tail_base), d_flags + 1,
-        d_flags + 1 + MAX_ROUNDS, d_maxn);
-    HIP_TRY(hipGetLastError());
-  }
-  const uint32_t lmax = finish_enabled(ctx, m) ? ctx->fin_lmax : 0u;
-  k_round_params<<<1, 64, 0, st>>>(d_flags + 1, lanes_max, ROUND_WG, g.kmin, P<uint4>(ctx->rparams), d_maxn, lmax);
-  HIP_TRY(hipGetLastError());
-  if (prof) ECC_TRY(record(ctx, 1, st));
-
-  uint32_t counts[MAX_ROUNDS], tails[MAX_ROUNDS];
-  // rounds launched (eager: those with work, up to the hand-over to the
-  // finishing pass; graph: the bound, each reading its own parameters)
-  int nr = g.B ? std::max(1, g.rounds) : 0;
-  bool finish = g.B != 0 && !exact_rounds && lmax != 0;
+  int nr = 0;
   uint64_t adds = 0;
-  if (exact_rounds) {
-    HIP_TRY(hipMemcpyAsync(ctx->host_small, d_flags, (2 + 2 * MAX_ROUNDS) * 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    memcpy(counts, ctx->host_small + 1, sizeof(counts));
-    memcpy(tails, ctx->host_small + 1 + MAX_ROUNDS, sizeof(tails));
-    int with_work = 0;
-    while (with_work < MAX_ROUNDS && (counts[with_work] || tails[with_work])) with_work++;
-    nr = int(finish_round(counts, ctx->host_small[1 + 2 * MAX_ROUNDS], uint32_t(with_work), lmax, 2 * lanes_max));
-    finish = nr < with_work;
-    for (int r = 0; r < nr; r++) adds += counts[r];  // the batch-affine additions of the rounds run
-  }
-  const Planes<C> A = planes<C>(ctx->slots, g.slot_cap), Bp = planes<C>(ctx->slots2, g.slot_cap);
-  for (int r = 0; r < nr; r++) {
-    const Planes<C>& out = (r & 1) ? Bp : A;
-    const Planes<C>& in = (r & 1) ? A : Bp;  // the previous round's output (unused in round 0)
-    if (prof) ECC_TRY(record(ctx, 2 + 2 * r, st));
-    uint32_t blocks = lanes_max / ROUND_WG;
-    if (exact_rounds) blocks = round_lane_count(counts[r], lanes_max, ROUND_WG, g.kmin) / ROUND_WG;
-    if (ctx->round_variant & RV_KERNEL_MASK) {
-      const size_t chain_words = (g.E / 2 + 1 + lanes_max + ROUND_WG) * C::F::NL;
-      HIP_TRY(launch_round_variant_bls(ctx->round_variant & RV_KERNEL_MASK, blocks, st, P<uint32_t>(ctx->bases),
-                                       P<uint32_t>(ctx->sorted), in.x, in.y, out.x, out.y,
-                                       P<uint2>(ctx->desc) + g.desc_base[r], P<uint4>(ctx->rparams) + r,
-                                       r == 0 ? 1 : 0, P<uint32_t>(ctx->mscr), P<uint2>(ctx->tails) + g.tail_base[r],
-                                       d_flags + 1 + MAX_ROUNDS + r, P<uint32_t>(ctx->mscr) + chain_words));
-    } else {
-      launch_round<C>(g.occ, blocks, st, P<uint32_t>(ctx->bases), P<uint32_t>(ctx->sorted), in.x, in.y, out.x,
-                      out.y, P<uint2>(ctx->desc) + g.desc_base[r], P<uint4>(ctx->rparams) + r, r == 0 ? 1 : 0,
-                      P<uint32_t>(ctx->mscr), P<uint2>(ctx->tails) + g.tail_base[r], d_flags + 1 + MAX_ROUNDS + r);
-      HIP_TRY(hipGetLastError());
-    }
-    if (prof) ECC_TRY(record(ctx, 3 + 2 * r, st));
-  }
-  if (finish) {
-    // the rounds left out: each bucket's remaining partial sums on its own lane
-    if (prof) ECC_TRY(record(ctx, 2 + 2 * nr, st));
-    k_bucket_finish<C, FINISH_WG><<<ceil_div(g.B, FINISH_WG), FINISH_WG, 0, st>>>(
-        P<uint32_t>(ctx->counts), P<uint32_t>(ctx->offsets), uint32_t(g.B), A.x, A.y, Bp.x, Bp.y,
-        P<uint32_t>(ctx->fzz), P<uint4>(ctx->rparams) + MAX_ROUNDS);
-    HIP_TRY(hipGetLastError());
-    if (prof) ECC_TRY(record(ctx, 3 + 2 * nr, st));
-  }
-  if (g.waves.size()) {
-    // bucket sums in XYZZ form where the finishing pass ran (or, in a graph,
-    // may run: then the reduction reads from the device whether it did)
-    const unsigned blocks = unsigned(ceil_div(g.waves.size() * 64, REDUCE_WG));
-    if (finish) {
-      k_reduce_a<C, REDUCE_WG, true><<<blocks, REDUCE_WG, 0, st>>>(
-          P<uint32_t>(ctx->counts), P<uint32_t>(ctx->offsets), A.x, A.y, Bp.x, Bp.y, GP<RedJob>(ctx, g.off_jobs),
-          GP<RedWave>(ctx, g.off_waves), uint32_t(g.waves.size()), P<uint32_t>(ctx->segS), P<uint32_t>(ctx->segT),
-          P<uint32_t>(ctx->winsum), P<uint32_t>(ctx->fzz), P<uint4>(ctx->rparams) + MAX_ROUNDS);
-    } else {
-      k_reduce_a<C, REDUCE_WG><<<blocks, REDUCE_WG, 0, st>>>(
-          P<uint32_t>(ctx->counts), P<uint32_t>(ctx->offsets), A.x, A.y, Bp.x, Bp.y, GP<RedJob>(ctx, g.off_jobs),
-          GP<RedWave>(ctx, g.off_waves), uint32_t(g.waves.size()), P<uint32_t>(ctx->segS), P<uint32_t>(ctx->segT),
-          P<uint32_t>(ctx->winsum));
-    }
-    HIP_TRY(hipGetLastError());
+  bool finish = false;
+  if (direct_sums(ctx)) {
+    ECC_TRY(enqueue_direct<C>(ctx, g, st, prof, &nr, &finish));
+  } else {
+    ECC_TRY(enqueue_rounds<C>(ctx, g, st, lanes_max, exact_rounds, &nr, &adds, &finish));
   }
   if (g.big.size()) {
     k_reduce_b<C><<<uint32_t(g.big.size()) * REDB_PARTS, 64 * REDB_WAVES, 0, st>>>(
@@ -789,7 +882,16 @@ ecc_status msm_batch_impl(ecc_ctx* ctx, const uint64_t* bases_in, const uint64_t
     HIP_TRY(hipMemcpyAsync(out_inf, d_inf, m, hipMemcpyDeviceToHost, st));
   }
   HIP_TRY(hipStreamSynchronize(st));
-  if (ctx->profiling && !use_graph) account(ctx, g.n, nr, adds, m, finished);
+  if (ctx->profiling && !use_graph) {
+    if (direct_sums(ctx) && g.B) {
+      // additions of the accumulation: entries less work items
+      HIP_TRY(hipMemcpyAsync(ctx->host_small, P<uint32_t>(ctx->ameta), 4, hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipMemcpyAsync(ctx->host_small + 1, P<uint32_t>(ctx->offsets) + g.B, 4, hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipStreamSynchronize(st));
+      adds = uint64_t(ctx->host_small[1]) - ctx->host_small[0];
+    }
+    account(ctx, g.n, nr, adds, m, finished);
+  }
   return ECC_OK;
 }
 

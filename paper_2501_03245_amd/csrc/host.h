@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "ecc_mi.h"
+#include "accumulate.h"
 #include "kernels.h"
 #include "verify.h"
 
@@ -89,6 +90,7 @@ struct ecc_ctx {
   DevBuf dig, part;                // digit codes and coarse-grouped entries of the bucket sort
   DevBuf hscal;                    // half-scalars of a batch with the endomorphism split
   DevBuf fzz;                      // ZZ, ZZZ of the bucket sums the finishing pass leaves in XYZZ form
+  DevBuf psum, aitems, acuts, ameta;  // bucket accumulation: sums, work items, cut buckets, counters
   DevBuf geo;                      // launch geometry tables of the current call
   // tables of the signing curves (secp256r1, SM2), by curve id, in the working form:
   DevBuf gtab[5];                  // 2^j G, j < 256 (batched-affine verification)
@@ -128,7 +130,8 @@ std::vector<DevBuf*> scratch_bufs(ecc_ctx* ctx) {
           &ctx->slots,   &ctx->slots2,  &ctx->desc,    &ctx->tails,   &ctx->mscr,      &ctx->segS,
           &ctx->segT,    &ctx->winsum,  &ctx->flags,   &ctx->scan_tmp, &ctx->stage_a,  &ctx->stage_b,
           &ctx->stage_c, &ctx->stage_d, &ctx->vscr,    &ctx->upts,    &ctx->rparams,   &ctx->hist,
-          &ctx->hist_scan, &ctx->dig,   &ctx->part,    &ctx->geo,     &ctx->hscal,     &ctx->fzz};
+          &ctx->hist_scan, &ctx->dig,   &ctx->part,    &ctx->geo,     &ctx->hscal,     &ctx->fzz,
+          &ctx->psum,    &ctx->aitems,  &ctx->acuts,   &ctx->ameta};
 }
 
 }  // namespace

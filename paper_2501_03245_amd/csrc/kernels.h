@@ -1277,9 +1277,11 @@ static __global__ void k_round_params(const uint32_t* __restrict__ counts, uint3
   params[MAX_ROUNDS] = make_uint4(R, nr, 0u, 0u);
 }
 
-// Design variants of the round kernel, for ablations of the choices the paper
-// makes for batch PADD (Section 3.3).  The default (0) is the library's form;
-// each bit switches one choice off.  Every variant computes the same sums.
+// Design variants of the bucket accumulation, for ablations of the choices the
+// paper makes for batch PADD (Section 3.3).  The default (0) is the direct sum
+// of accumulate.h; any other value runs the rounds of this file, and each of
+// the kernel bits switches one choice of theirs off.  Every variant computes
+// the same sums.
 enum : int {
   RV_STORE_DENOM = 1,  // store each denominator in the compress step and load it
                        // back in the decompress step instead of recomputing it
@@ -1297,7 +1299,7 @@ enum : int {
                        // decompress step recomputes an odd step's M_i = M_{i-1} d_{i-1}
                        // (one more product per two additions, half the chain traffic)
   // host-side choices of where the rounds stop (the round kernel is unchanged):
-  // by default a single MSM stops them early and adds each bucket's last
+  // without them a single MSM stops them early and adds each bucket's last
   // partial sums on its own lane (k_bucket_finish), a batch runs them to the end
   RV_FINISH = 16,      // the finishing pass for batches too
   RV_ROUNDS_ONLY = 32, // rounds to the end for every call (the paper's form)
@@ -1353,7 +1355,7 @@ __device__ __forceinline__ void round_priority(uint32_t done, uint32_t total) {
 // from device memory (written by k_round_params after planning), so the
 // launch needs no host round trip; lanes beyond T leave at once.
 // OCC: waves per SIMD the register allocation aims at (a tuning knob);
-// V: design variant (RV_* bits, 0 in the library's own path).  dscr is the
+// V: design variant of the kernel (RV_* bits).  dscr is the
 // stored-denominator area of RV_STORE_DENOM (laid out like mscr).
 template <class C, int WG, int OCC, int V = 0>
 __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(OCC))) k_bucket_round(const uint32_t* __restrict__ bases,
