@@ -224,7 +224,7 @@ ecc_status ecc_msm_batch_scratch_bytes(ecc_ctx *ctx, ecc_curve curve, const uint
  *    few requests it holds;
  *  - per lane (ECC_VERIFY_PER_LANE): each request's double-scalar sum in XYZZ
  *    coordinates on its own lane (4-bit windows of u2 over a per-request table
- *    of d Q, a comb table of d 2^(8 j) G for u1), with two batched inversions
+ *    of d Q, a comb table of G for u1), with two batched inversions
  *    per launch.  This is the default: it measured faster at every batch
  *    size, in latency and in throughput.
  * The inverses of s mod n are batched per workgroup in both.
@@ -249,7 +249,7 @@ ecc_status ecc_verify_batch(ecc_ctx *ctx, ecc_curve curve, const uint8_t *hashes
  * and valid are DEVICE pointers with the layouts of ecc_verify_batch, owned
  * by the caller.  The device memory the work needs (the generator's comb
  * tables and one table of d Q per request) is a fixed array inside the
- * library, about 28 MB on every GPU the call runs on, held until the process
+ * library, about 15 MB on every GPU the call runs on, held until the process
  * ends; the first call on a device builds the comb tables there.  Every call
  * on one GPU uses that same array: calls that overlap on one GPU (from
  * several threads or streams) race, so the caller orders them.  At most
@@ -266,7 +266,7 @@ size_t ecc_verify_batch_noalloc_max(void);
  * multiplication and one inversion mod n per request (Section 5.2).
  * Request i: with 1 <= d_i, k_i <= n - 1, R = k_i G, r = R.x mod n,
  * e = the hash read as a big-endian integer, s = k_i^-1 (e + r d_i) mod n.
- * k_i G is summed from a comb table of d 2^(8 j) G (made once per context)
+ * k_i G is summed from a comb table of G (made once per context)
  * in XYZZ coordinates, one request per lane; R.x's denominator and k_i are
  * inverted by one Gather-Apply-Scatter batch inversion each per workgroup.
  *   hashes   : m x 32 bytes (big-endian digests)
@@ -308,8 +308,8 @@ ecc_status ecc_pmul_batch(ecc_ctx *ctx, ecc_curve curve, const uint64_t *points,
 
 /* k_i G for the curve's standard generator G (fixed-point multiplication,
  * the paper's FPMUL with precomputed multiples of G, Section 2.1): one mixed
- * addition per byte of k_i, of d 2^(8 j) G from a comb table that the
- * context makes once per curve with the double-and-add of Algorithm 1, then
+ * addition per signed digit of k_i (13 bits; 8 bits in a context with an HBM
+ * budget) from a comb table that the context makes once per curve, then
  * one batched inversion for the affine results.  ks: n x 4 u64 scalars (any
  * 256-bit value); out: n points, canonical affine ((0,0) when k_i G is the
  * point at infinity).  Also used to produce seeded bases P_i = k_i G. */

@@ -24,11 +24,11 @@ ecc_status fixed_base_impl(ecc_ctx* ctx, const uint64_t* ks, size_t n, uint64_t*
     d_k = P<uint32_t>(ctx->stage_a);
     d_out = P<uint32_t>(ctx->stage_b);
   }
-  // one mixed addition per scalar byte from the comb table (made by the
-  // double-and-add kernel on the first call)
-  ECC_TRY(ensure_gcomb<C>(ctx, st));
-  k_fixed_base_comb<C, 256><<<ceil_div(n, 256), 256, 0, st>>>(d_k, n, P<uint32_t>(ctx->gcomb[C::ID]), d_out,
-                                                              (flags & ECC_IN_MONTGOMERY) ? 1 : 0);
+  ECC_TRY(ensure_gcomb<C>(ctx, st));  // made on the first call
+  with_comb_width(ctx, [&](auto w) {
+    k_fixed_base_comb<C, 256, decltype(w)::value><<<ceil_div(n, 256), 256, 0, st>>>(
+        d_k, n, P<uint32_t>(ctx->gcomb[C::ID]), d_out, (flags & ECC_IN_MONTGOMERY) ? 1 : 0);
+  });
   HIP_TRY(hipGetLastError());
   if (host) HIP_TRY(hipMemcpyAsync(out, d_out, n * PW * 4, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -59,34 +59,28 @@ ecc_status ensure_gtab(ecc_ctx* ctx, hipStream_t st) {
   return ECC_OK;
 }
 
-// the comb table of the per-lane verification and of signing: d 2^(8 j) G
-// for j < 32 and d < 256 in the working form, entry (j, d) at j 256 + d
-// (entry d = 0 holds 2^(8 j) G and is never read); made once per context and
-// curve by the fixed-base kernel
+// The comb table of the generator (verify.h), made once per context and curve.
+// A context with a cap on its device memory keeps the narrow table, so that
+// the wide one (8 to 11 MB) never takes what a call that fitted before needs.
 template <class C>
 ecc_status ensure_gcomb(ecc_ctx* ctx, hipStream_t st) {
   if (ctx->gcomb_ready[C::ID]) return ECC_OK;
-  constexpr int IOW = 2 * C::F::N32;
-  constexpr size_t NE = size_t(VCOMB_WINDOWS) * VCOMB_ENTRIES;
-  ECC_TRY(ensure(ctx, ctx->gcomb[C::ID], NE * affine_words<C>() * 4));
-  ECC_TRY(ensure(ctx, ctx->stage_d, NE * 32 + NE * IOW * 4 + 256));
-  std::vector<uint64_t> ks(NE * 4, 0);
-  for (int j = 0; j < VCOMB_WINDOWS; j++)
-    for (int d = 0; d < VCOMB_ENTRIES; d++)
-      ks[(size_t(j) * VCOMB_ENTRIES + d) * 4 + (8 * j) / 64] = uint64_t(d == 0 ? 1 : d) << ((8 * j) % 64);
-  uint32_t* d_k = P<uint32_t>(ctx->stage_d);
-  uint32_t* d_pts = d_k + NE * 8;
-  uint32_t* d_err = d_pts + NE * IOW;
-  HIP_TRY(hipMemcpyAsync(d_k, ks.data(), ks.size() * 8, hipMemcpyHostToDevice, st));
-  ECC_TRY(fill_u32(ctx, d_err, 1, 0u, st));
-  k_fixed_base<C, 256><<<unsigned(ceil_div(NE, 256)), 256, 0, st>>>(d_k, NE, d_pts, 0);
-  HIP_TRY(hipGetLastError());
-  k_ingest_points<C><<<unsigned(ceil_div(NE, 256)), 256, 0, st>>>(d_pts, P<uint32_t>(ctx->gcomb[C::ID]), nullptr, NE,
-                                                                  0, 0, d_err);
+  const bool wide = ctx->budget == 0;
+  const size_t ne = wide ? comb_entries<COMB_WIDE>() : comb_entries<COMB_NARROW>();
+  ECC_TRY(ensure(ctx, ctx->gcomb[C::ID], ne * affine_words<C>() * 4));
+  if (wide) k_comb_build<C, COMB_WIDE, 256><<<ceil_div(ne, 256), 256, 0, st>>>(P<uint32_t>(ctx->gcomb[C::ID]));
+  else k_comb_build<C, COMB_NARROW, 256><<<ceil_div(ne, 256), 256, 0, st>>>(P<uint32_t>(ctx->gcomb[C::ID]));
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(st));
   ctx->gcomb_ready[C::ID] = true;
   return ECC_OK;
+}
+
+// run fn with the width of the context's comb table as a compile-time constant
+template <class Fn>
+void with_comb_width(const ecc_ctx* ctx, Fn fn) {
+  if (ctx->budget == 0) fn(std::integral_constant<int, COMB_WIDE>{});
+  else fn(std::integral_constant<int, COMB_NARROW>{});
 }
 
 template <class C>
@@ -126,9 +120,11 @@ ecc_status verify_impl(ecc_ctx* ctx, const uint8_t* hashes, const uint64_t* pubk
   if (per_lane) {
     for (size_t off = 0; off < m; off += VERIFY_LANE_CHUNK) {
       const size_t c = std::min(VERIFY_LANE_CHUNK, m - off);
-      k_verify_xyzz<C, VERIFY_LANE_WG><<<ceil_div(c, VERIFY_LANE_WG), VERIFY_LANE_WG, 0, st>>>(
-          d_h + off * 32, d_q + off * 16, d_s + off * 16, c, P<uint32_t>(ctx->gcomb[C::ID]), P<uint32_t>(ctx->vscr),
-          d_v + off);
+      with_comb_width(ctx, [&](auto w) {
+        k_verify_xyzz<C, VERIFY_LANE_WG, decltype(w)::value><<<ceil_div(c, VERIFY_LANE_WG), VERIFY_LANE_WG, 0, st>>>(
+            d_h + off * 32, d_q + off * 16, d_s + off * 16, c, P<uint32_t>(ctx->gcomb[C::ID]),
+            P<uint32_t>(ctx->vscr), d_v + off);
+      });
       HIP_TRY(hipGetLastError());
     }
   } else {
@@ -169,7 +165,10 @@ ecc_status sign_impl(ecc_ctx* ctx, const uint8_t* hashes, const uint64_t* privke
     d_h = P<uint8_t>(ctx->stage_c);
     d_s = reinterpret_cast<uint32_t*>(P<uint8_t>(ctx->stage_c) + m * 32);
   }
-  k_sign<C, SIGN_WG><<<ceil_div(m, SIGN_WG), SIGN_WG, 0, st>>>(d_h, d_d, d_k, m, P<uint32_t>(ctx->gcomb[C::ID]), d_s);
+  with_comb_width(ctx, [&](auto w) {
+    k_sign<C, SIGN_WG, decltype(w)::value><<<ceil_div(m, SIGN_WG), SIGN_WG, 0, st>>>(
+        d_h, d_d, d_k, m, P<uint32_t>(ctx->gcomb[C::ID]), d_s);
+  });
   HIP_TRY(hipGetLastError());
   if (host) HIP_TRY(hipMemcpyAsync(sigs, d_s, m * 64, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));

@@ -95,7 +95,7 @@ struct ecc_ctx {
   // tables of the signing curves (secp256r1, SM2), by curve id, in the working form:
   DevBuf gtab[5];                  // 2^j G, j < 256 (batched-affine verification)
   bool gtab_ready[5] = {};
-  DevBuf gcomb[5];                 // d 2^(8 j) G, j < 32, d < 256 (fixed-base products, per-lane verification, signing)
+  DevBuf gcomb[5];                 // comb table of G (fixed-base products, per-lane verification, signing)
   bool gcomb_ready[5] = {};
   DevBuf vscr;                     // per-lane verification and point multiplication: each lane's table of d Q
   DevBuf upts;                     // point multiplication: the points in the working form
