@@ -46,7 +46,7 @@ constexpr int REDUCE_MAX_SHRINK = 4;
 constexpr size_t GRAPH_CACHE = 16;
 constexpr int VERIFY_WG = 256;
 constexpr int VERIFY_LANE_WG = 64;                       // per-lane verification: one wave per workgroup
-constexpr size_t VERIFY_LANE_CHUNK = size_t(1) << 16;    // requests per launch of the per-lane form
+constexpr size_t VERIFY_LANE_CHUNK = size_t(1) << 17;    // requests per launch of the per-lane form
 constexpr int SIGN_WG = 256;
 constexpr int PMUL_WG = 64;
 constexpr int UPMUL_WG = 256;       // batch UPMUL (Algorithm 3): lanes per workgroup

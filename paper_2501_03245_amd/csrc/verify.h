@@ -282,15 +282,18 @@ __global__ void __launch_bounds__(WG) k_verify(const uint8_t* __restrict__ hashe
 // Measured (one call, unsigned limbs with fifteen-entry tables before): 2^19
 // SM2 products 14.36 -> 9.33 ms, 3001 BN254 products 1.78 -> 1.14 ms, 2^16 SM2
 // verifications 1.84 -> 1.52 ms, 2^18 SM2 signatures 0.695 -> 0.614 ms, 2^19
-// SM2 fixed-point products 1.20 -> 1.00 ms.
+// SM2 fixed-point products 1.20 -> 1.00 ms.  Two waves on each SIMD (at most 256
+// registers, 2^17 requests a launch) instead of one: 2^19 SM2 products 9.65 ->
+// 8.49 ms; three waves take 9.77 ms (spilled registers), and so would two on
+// BLS12-381, which keeps one.
 
 constexpr int VT_N = 8;             // table entries d Q, d = 1..8
 
-// words per table entry: X, Y, ZZ, ZZZ, the chain prefix and a flag word,
-// rounded up to whole 16-byte groups
+// words per table entry: X, Y, Z, the chain prefix and a flag word, rounded up
+// to whole 16-byte groups
 template <class F>
 constexpr int vt_slot() {
-  return (5 * F::NL + 1 + 3) / 4 * 4;
+  return (4 * F::NL + 1 + 3) / 4 * 4;
 }
 
 // every access to a table slot is a 16-byte vector access (one access type
@@ -377,10 +380,10 @@ __device__ __forceinline__ uint32_t take_top(uint32_t (&a)[8]) {
   return d;
 }
 
-// This lane's table T[d] = d Q (d = 1..VT_N) as affine entries: made in XYZZ
-// coordinates, then normalised with one Montgomery-trick chain over the ZZZ
-// and one Gather-Apply-Scatter inversion for the workgroup (every lane must
-// call it).  An entry that is O (Q of order at most 8, possible only off the
+// This lane's table T[d] = d Q (d = 1..VT_N) as affine entries: made in
+// Jacobian coordinates, then normalised with one Montgomery-trick chain over
+// the Z and one Gather-Apply-Scatter inversion for the workgroup (every lane
+// must call it).  An entry that is O (Q of order at most 8, possible only off the
 // prime-order subgroup) puts 1 into the chain and is stored as the infinity
 // marker, which the mixed addition skips.  Q itself must not be O.
 template <class C, int WG>
@@ -391,23 +394,22 @@ __device__ __forceinline__ void vt_build(uint32_t* __restrict__ tab, const Affin
   constexpr int SLOT = vt_slot<F>();
   static_assert(vt_affine_words<F>() <= SLOT, "affine entry inside its slot");
   const Lz<F> qx = lz_of<F>(Q.x), qy = lz_of<F>(Q.y);
-  Xz<C> T;
-  xz_mdbl<C>(T, qx, qy);  // no curve here has a point of order 2
+  Jz<C> T;
+  jz_mdbl<C>(T, qx, qy);  // no curve here has a point of order 2
   bool inf = false;
   Lz<F> pref = lz_one<F>();
 #pragma unroll 1
   for (int d = 2; d <= VT_N; d++) {
-    const Lz<F> z = lz_select<F>(inf, lz_one<F>(), T.ZZZ);
+    const Lz<F> z = lz_select<F>(inf, lz_one<F>(), T.Z);
     uint32_t w[SLOT] = {};
     vt_pack<F>(w, T.X);
     vt_pack<F>(w + NL, T.Y);
-    vt_pack<F>(w + 2 * NL, T.ZZ);
-    vt_pack<F>(w + 3 * NL, z);
-    vt_pack<F>(w + 4 * NL, pref);
-    w[5 * NL] = inf ? 1u : 0u;
+    vt_pack<F>(w + 2 * NL, z);
+    vt_pack<F>(w + 3 * NL, pref);
+    w[4 * NL] = inf ? 1u : 0u;
     vt_store(tab + (d - 1) * SLOT, w);
     pref = lz_mul<F>(pref, z);
-    if (d < VT_N) xz_madd<C>(T, inf, qx, qy);
+    if (d < VT_N) jz_madd<C>(T, inf, qx, qy);
   }
   Lz<F> inv = lz_of<F>(wg_batch_inverse<F, WG, 4>(lz_semi<F>(pref), s_tot, s_inv));
 #pragma unroll 1
@@ -415,12 +417,12 @@ __device__ __forceinline__ void vt_build(uint32_t* __restrict__ tab, const Affin
     uint32_t* sl = tab + (d - 1) * SLOT;
     uint32_t w[SLOT];
     vt_load(sl, w);
-    const Lz<F> t = lz_mul<F>(inv, vt_unpack<F>(w + 4 * NL));  // 1 / ZZZ_d
-    inv = lz_mul<F>(inv, vt_unpack<F>(w + 3 * NL));            // 1 / (ZZZ_2 ... ZZZ_(d-1))
-    const Lz<F> iz = lz_mul<F>(vt_unpack<F>(w + 2 * NL), t);   // 1 / Z (ZZ = Z^2, ZZZ = Z^3)
-    Lz<F> x = lz_mul<F>(vt_unpack<F>(w), lz_sqr<F>(iz));
-    const Lz<F> y = lz_mul<F>(vt_unpack<F>(w + NL), t);
-    if (w[5 * NL]) x = lz_of<F>(fp_inf_marker<F>());
+    const Lz<F> iz = lz_mul<F>(inv, vt_unpack<F>(w + 3 * NL));  // 1 / Z_d
+    inv = lz_mul<F>(inv, vt_unpack<F>(w + 2 * NL));             // 1 / (Z_2 ... Z_(d-1))
+    const Lz<F> iz2 = lz_sqr<F>(iz);
+    Lz<F> x = lz_mul<F>(vt_unpack<F>(w), iz2);
+    const Lz<F> y = lz_mul<F>(vt_unpack<F>(w + NL), lz_mul<F>(iz, iz2));
+    if (w[4 * NL]) x = lz_of<F>(fp_inf_marker<F>());
     vt_put_affine<C>(sl, x, y);
   }
   vt_put_affine<C>(tab, qx, qy);
@@ -621,7 +623,7 @@ __device__ __forceinline__ bool x_is(const Xz<C>& A, const uint32_t (&v)[8]) {
 
 // scratch: VT_N * vt_slot<F>() words per lane of the grid (dead lanes included)
 template <class C, int WG, int W>
-__global__ void __launch_bounds__(WG) k_verify_xyzz(const uint8_t* __restrict__ hashes,
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) k_verify_xyzz(const uint8_t* __restrict__ hashes,
                                                     const uint32_t* __restrict__ pubkeys,
                                                     const uint32_t* __restrict__ sigs, size_t m,
                                                     const uint32_t* __restrict__ gcomb,
@@ -759,7 +761,7 @@ __global__ void __launch_bounds__(WG) k_sign(const uint8_t* __restrict__ hashes,
 // per workgroup.  pts are working-form affine points (the infinity
 // marker for O); every k_i is a 256-bit integer, taken as is.
 template <class C, int WG>
-__global__ void __launch_bounds__(WG) k_pmul(const uint32_t* __restrict__ pts, const uint32_t* __restrict__ ks,
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(C::NL > 10 ? 1 : 2))) k_pmul(const uint32_t* __restrict__ pts, const uint32_t* __restrict__ ks,
                                              size_t n, uint32_t* __restrict__ scratch, uint32_t* __restrict__ out,
                                              int out_mont) {
   using F = typename C::F;
