@@ -614,6 +614,103 @@ __device__ __forceinline__ void store_lz_affine(const Lz<typename C::F>& x, cons
   }
 }
 
+// ---- the endomorphism split of one product ---------------------------------------
+// On a curve whose every point is in the order-r subgroup (BN254: cofactor 1)
+// k P = k1 P + k2 phi(P) with half-length k1, k2 (the split of the MSMs), which
+// halves the doublings: 3001 products 1.14 -> 0.86 ms.  BLS12-381 has points
+// outside the subgroup, which this call accepts, so it keeps the full scalar.
+template <class C>
+constexpr bool vt_glv() {
+  return C::ID == BN254::ID;
+}
+
+// k mod r for any 256-bit k (2^256 < 6 r on BN254)
+template <class C>
+__device__ __forceinline__ void reduce_order(uint32_t (&k)[8]) {
+  constexpr Words<8> r = C::ORDER;
+#pragma unroll 1
+  for (int t = 0; t < 5; t++) {
+    if (words_lt8(k, r.w)) break;
+    int64_t br = 0;
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      br += int64_t(k[i]) - int64_t(r.w[i]);
+      k[i] = uint32_t(br);
+      br >>= 32;
+    }
+  }
+}
+
+// words of a slot before beta x of its entry
+template <class F>
+constexpr int vt_beta_at() {
+  return vt_affine_words<F>();
+}
+
+// A = k Q for the Q of this lane's table; k is consumed
+template <class C>
+__device__ __forceinline__ void vt_mul_glv(Jz<C>& A, bool& inf, uint32_t* __restrict__ tab, uint32_t (&k)[8]) {
+  using F = typename C::F;
+  constexpr int NL = F::NL;
+  constexpr int XW = (NL + 3) / 4 * 4;
+  static_assert(vt_beta_at<F>() + XW <= vt_slot<F>(), "beta x inside its slot");
+  static_assert(Glv<C>::BITS <= 126, "the signed nibbles of a half end in 128 bits");
+  reduce_order<C>(k);
+  uint32_t m1[8], m2[8];
+  bool n1, n2;
+  glv_split<C>(k, m1, n1, m2, n2);  // |halves| < 2^BITS for every k < r
+  constexpr Words<NL> beta = Glv<C>::BETA;
+#pragma unroll 1
+  for (int d = 0; d < VT_N; d++) {
+    uint32_t w[XW] = {};
+    vt_pack<F>(w, lz_mul<F>(vt_get_affine<C>(tab + d * vt_slot<F>()).x, lz_of<F>(fp_from<F>(beta))));
+    vt_store(tab + d * vt_slot<F>() + vt_beta_at<F>(), w);
+  }
+  // 128-bit signed nibbles, no carry out of the halves; the digits are then
+  // taken from the top of words 4..7
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    m1[i + 4] = m1[i];
+    m2[i + 4] = m2[i];
+    m1[i] = m2[i] = 0;
+  }
+  uint64_t c1 = 0, c2 = 0;
+#pragma unroll
+  for (int i = 4; i < 8; i++) {
+    c1 += uint64_t(m1[i]) + 0x88888888u;
+    c2 += uint64_t(m2[i]) + 0x88888888u;
+    m1[i] = uint32_t(c1);
+    m2[i] = uint32_t(c2);
+    c1 >>= 32;
+    c2 >>= 32;
+  }
+  inf = true;
+  const LzAffine<C> Q = vt_get_affine<C>(tab);
+  A.X = Q.x;
+  A.Y = Q.y;
+  A.Z = lz_one<F>();
+#pragma unroll 1
+  for (int w = 31; w >= 0; w--) {
+#pragma unroll 1
+    for (int i = 0; i < 4; i++) jz_dbl<C>(A);
+    // the two additions as one piece of code
+#pragma unroll 1
+    for (int h = 0; h < 2; h++) {
+      const int f = int(h ? take_top<4>(m2) : take_top<4>(m1)) - 8;
+      const int d = (h ? n2 : n1) ? -f : f;
+      if (d == 0) continue;
+      const uint32_t* sl = tab + ((d < 0 ? -d : d) - 1) * vt_slot<F>();
+      LzAffine<C> T = vt_get_affine<C>(sl);
+      if (h) {
+        uint32_t bw[XW];
+        vt_load(sl + vt_beta_at<F>(), bw);
+        T.x = vt_unpack<F>(bw);
+      }
+      jz_madd<C>(A, inf, T.x, lz_neg_if<F>(T.y, d < 0));
+    }
+  }
+}
+
 // X / ZZ = v for a canonical 256-bit v < p
 template <class C>
 __device__ __forceinline__ bool x_is(const Xz<C>& A, const uint32_t (&v)[8]) {
@@ -786,7 +883,8 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(C::NL >
   vt_build<C, WG>(tab, P, s_tot, s_inv);
   Jz<C> A;
   bool inf;
-  vt_mul<C>(A, inf, tab, k);
+  if constexpr (vt_glv<C>()) vt_mul_glv<C>(A, inf, tab, k);
+  else vt_mul<C>(A, inf, tab, k);
   inf = inf || pinf;
   const Lz<F> iz = lz_of<F>(wg_batch_inverse<F, WG>(inf ? fp_one<F>() : lz_semi<F>(A.Z), s_tot, s_inv));
   const Lz<F> iz2 = lz_sqr<F>(iz);

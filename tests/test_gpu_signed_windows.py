@@ -23,7 +23,9 @@ def window_edges(c):
     one = [d << s for d in (7, 8, 9, 15, 16, 17) for s in (0, 4, 124, 128, 248, 252)]
     # k P = (d 16^j) P + (r - d 16^j) P: the running sum passes through or next to O
     wrap = [(r + e) * m for e in (-9, -8, -7, -1, 0, 1, 7, 8, 9) for m in (1, 2, 15)]
-    return [v & top for v in rep + one + wrap + [top, top - 7, top - 8, 1 << 255, (1 << 255) - 1, 0, 8 * r + 8]]
+    # around every multiple of the order below 2^256
+    multi = [m * r + e for m in range(1, top // r + 1) for e in (-1, 0, 1)]
+    return [v & top for v in rep + one + wrap + multi + [top, top - 7, top - 8, 1 << 255, (1 << 255) - 1, 0, 8 * r + 8]]
 
 
 @pytest.mark.parametrize("name", ["bn254", "bls12_381", "secp256r1", "sm2"])
