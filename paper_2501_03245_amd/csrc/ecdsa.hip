@@ -26,8 +26,11 @@ ecc_status fixed_base_impl(ecc_ctx* ctx, const uint64_t* ks, size_t n, uint64_t*
   }
   ECC_TRY(ensure_gcomb<C>(ctx, st));  // made on the first call
   with_comb_width(ctx, [&](auto w) {
-    k_fixed_base_comb<C, 256, decltype(w)::value><<<ceil_div(n, 256), 256, 0, st>>>(
-        d_k, n, P<uint32_t>(ctx->gcomb[C::ID]), d_out, (flags & ECC_IN_MONTGOMERY) ? 1 : 0);
+    with_lanes(n, [&](auto l) {
+      constexpr int L = decltype(l)::value;
+      k_fixed_base_comb<C, 256, decltype(w)::value, L><<<ceil_div(n * L, 256), 256, 0, st>>>(
+          d_k, n, P<uint32_t>(ctx->gcomb[C::ID]), d_out, (flags & ECC_IN_MONTGOMERY) ? 1 : 0);
+    });
   });
   HIP_TRY(hipGetLastError());
   if (host) HIP_TRY(hipMemcpyAsync(out, d_out, n * PW * 4, hipMemcpyDeviceToHost, st));
@@ -76,6 +79,20 @@ ecc_status ensure_gcomb(ecc_ctx* ctx, hipStream_t st) {
   return ECC_OK;
 }
 
+// run fn with the lanes per request of a call of n requests as a compile-time constant
+template <class Fn>
+void with_lanes(size_t n, Fn fn) {
+  if (n <= QUAD_MAX) fn(std::integral_constant<int, 4>{});
+  else fn(std::integral_constant<int, 1>{});
+}
+
+// scratch of the per-request tables of a call of n requests, in words
+template <class F>
+size_t table_words(size_t n, size_t wg) {
+  if (n <= QUAD_MAX) return ceil_div(n * 4, wg) * wg / 4 * VT_N * qvt_slot<F>();
+  return ceil_div(std::min(n, VERIFY_LANE_CHUNK), wg) * wg * VT_N * vt_slot<F>();
+}
+
 // run fn with the width of the context's comb table as a compile-time constant
 template <class Fn>
 void with_comb_width(const ecc_ctx* ctx, Fn fn) {
@@ -96,8 +113,7 @@ ecc_status verify_impl(ecc_ctx* ctx, const uint8_t* hashes, const uint64_t* pubk
   const bool per_lane = !(flags & ECC_VERIFY_BATCHED);
   if (per_lane) {
     ECC_TRY(ensure_gcomb<C>(ctx, st));
-    const size_t lanes = ceil_div(std::min(m, VERIFY_LANE_CHUNK), VERIFY_LANE_WG) * VERIFY_LANE_WG;
-    ECC_TRY(ensure(ctx, ctx->vscr, lanes * VT_N * vt_slot<typename C::F>() * 4));
+    ECC_TRY(ensure(ctx, ctx->vscr, table_words<typename C::F>(m, VERIFY_LANE_WG) * 4));
   } else {
     ECC_TRY(ensure_gtab<C>(ctx, st));
   }
@@ -121,9 +137,13 @@ ecc_status verify_impl(ecc_ctx* ctx, const uint8_t* hashes, const uint64_t* pubk
     for (size_t off = 0; off < m; off += VERIFY_LANE_CHUNK) {
       const size_t c = std::min(VERIFY_LANE_CHUNK, m - off);
       with_comb_width(ctx, [&](auto w) {
-        k_verify_xyzz<C, VERIFY_LANE_WG, decltype(w)::value><<<ceil_div(c, VERIFY_LANE_WG), VERIFY_LANE_WG, 0, st>>>(
-            d_h + off * 32, d_q + off * 16, d_s + off * 16, c, P<uint32_t>(ctx->gcomb[C::ID]),
-            P<uint32_t>(ctx->vscr), d_v + off);
+        with_lanes(m, [&](auto l) {
+          constexpr int L = decltype(l)::value;
+          k_verify_xyzz<C, VERIFY_LANE_WG, decltype(w)::value, L>
+              <<<ceil_div(c * L, VERIFY_LANE_WG), VERIFY_LANE_WG, 0, st>>>(d_h + off * 32, d_q + off * 16, d_s + off * 16,
+                                                                           c, P<uint32_t>(ctx->gcomb[C::ID]),
+                                                                           P<uint32_t>(ctx->vscr), d_v + off);
+        });
       });
       HIP_TRY(hipGetLastError());
     }
@@ -166,8 +186,11 @@ ecc_status sign_impl(ecc_ctx* ctx, const uint8_t* hashes, const uint64_t* privke
     d_s = reinterpret_cast<uint32_t*>(P<uint8_t>(ctx->stage_c) + m * 32);
   }
   with_comb_width(ctx, [&](auto w) {
-    k_sign<C, SIGN_WG, decltype(w)::value><<<ceil_div(m, SIGN_WG), SIGN_WG, 0, st>>>(
-        d_h, d_d, d_k, m, P<uint32_t>(ctx->gcomb[C::ID]), d_s);
+    with_lanes(m, [&](auto l) {
+      constexpr int L = decltype(l)::value;
+      k_sign<C, SIGN_WG, decltype(w)::value, L><<<ceil_div(m * L, SIGN_WG), SIGN_WG, 0, st>>>(
+          d_h, d_d, d_k, m, P<uint32_t>(ctx->gcomb[C::ID]), d_s);
+    });
   });
   HIP_TRY(hipGetLastError());
   if (host) HIP_TRY(hipMemcpyAsync(sigs, d_s, m * 64, hipMemcpyDeviceToHost, st));
@@ -199,9 +222,8 @@ ecc_status pmul_impl(ecc_ctx* ctx, const uint64_t* pts, const uint64_t* ks, size
     d_k = P<uint32_t>(ctx->stage_b);
     d_out = P<uint32_t>(ctx->stage_c);
   }
-  const size_t lanes = ceil_div(std::min(n, VERIFY_LANE_CHUNK), PMUL_WG) * PMUL_WG;
   ECC_TRY(ensure(ctx, ctx->upts, n * PW * 4));
-  if (!(flags & ECC_PMUL_BATCHED)) ECC_TRY(ensure(ctx, ctx->vscr, lanes * VT_N * vt_slot<F>() * 4));
+  if (!(flags & ECC_PMUL_BATCHED)) ECC_TRY(ensure(ctx, ctx->vscr, table_words<F>(n, PMUL_WG) * 4));
   ECC_TRY(ensure(ctx, ctx->flags, 256));
   uint32_t* d_err = P<uint32_t>(ctx->flags);
   ECC_TRY(fill_u32(ctx, d_err, 1, 0u, st));
@@ -232,8 +254,11 @@ ecc_status pmul_impl(ecc_ctx* ctx, const uint64_t* pts, const uint64_t* ks, size
   }
   for (size_t off = 0; off < n && !(flags & ECC_PMUL_BATCHED); off += VERIFY_LANE_CHUNK) {
     const size_t c = std::min(VERIFY_LANE_CHUNK, n - off);
-    k_pmul<C, PMUL_WG><<<ceil_div(c, PMUL_WG), PMUL_WG, 0, st>>>(P<uint32_t>(ctx->upts) + off * PW, d_k + off * 8, c,
-                                                                 P<uint32_t>(ctx->vscr), d_out + off * IOW, mont);
+    with_lanes(n, [&](auto l) {
+      constexpr int L = decltype(l)::value;
+      k_pmul<C, PMUL_WG, L><<<ceil_div(c * L, PMUL_WG), PMUL_WG, 0, st>>>(
+          P<uint32_t>(ctx->upts) + off * PW, d_k + off * 8, c, P<uint32_t>(ctx->vscr), d_out + off * IOW, mont);
+    });
     HIP_TRY(hipGetLastError());
   }
   if (host) HIP_TRY(hipMemcpyAsync(out, d_out, n * IOW * 4, hipMemcpyDeviceToHost, st));

@@ -29,7 +29,8 @@ constexpr size_t comb_words() {
 
 template <class C>
 constexpr size_t table_words() {
-  return NOALLOC_MAX_REQUESTS * size_t(VT_N) * size_t(vt_slot<typename C::F>());
+  static_assert(NOALLOC_MAX_REQUESTS <= QUAD_MAX && NOALLOC_MAX_REQUESTS * 4 % VERIFY_LANE_WG == 0, "a quad per request");
+  return NOALLOC_MAX_REQUESTS * size_t(VT_N) * size_t(qvt_slot<typename C::F>());
 }
 
 constexpr size_t round_up64(size_t w) { return (w + 63) / 64 * 64; }
@@ -88,7 +89,7 @@ template <class C>
 ecc_status verify_noalloc(uint32_t* base, size_t comb_off, const uint8_t* hashes, const uint64_t* pubkeys,
                           const uint64_t* sigs, size_t m, uint8_t* valid, hipStream_t st) {
   static_assert(table_words<C>() <= TABLE_WORDS, "tables exceed the scratch array");
-  k_verify_xyzz<C, VERIFY_LANE_WG, COMB_NARROW><<<unsigned(ceil_div(m, VERIFY_LANE_WG)), VERIFY_LANE_WG, 0, st>>>(
+  k_verify_xyzz<C, VERIFY_LANE_WG, COMB_NARROW, 4><<<unsigned(ceil_div(m * 4, VERIFY_LANE_WG)), VERIFY_LANE_WG, 0, st>>>(
       hashes, reinterpret_cast<const uint32_t*>(pubkeys), reinterpret_cast<const uint32_t*>(sigs), m,
       base + comb_off, base + OFF_TABLES, valid);
   if (hipGetLastError() != hipSuccess) return ECC_ERR_DEVICE;

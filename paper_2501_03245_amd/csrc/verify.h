@@ -23,6 +23,7 @@
 #pragma once
 #include "kernels.h"
 #include "lazy.h"
+#include "quad.h"
 
 namespace eccmi {
 
@@ -641,6 +642,28 @@ __device__ __forceinline__ void reduce_order(uint32_t (&k)[8]) {
   }
 }
 
+// k -> the signed nibbles of |k1| (in k) and |k2|, 32 of them in words 4..7,
+// and the halves' signs
+template <class C>
+__device__ __forceinline__ void vt_split(uint32_t (&k)[8], uint32_t (&m2)[8], bool& n1, bool& n2) {
+  static_assert(Glv<C>::BITS <= 126, "the signed nibbles of a half end in 128 bits");
+  reduce_order<C>(k);
+  uint32_t m1[8];
+  glv_split<C>(k, m1, n1, m2, n2);  // |halves| < 2^BITS for every k < r
+  uint64_t c1 = 0, c2 = 0;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    c1 += uint64_t(m1[i]) + 0x88888888u;
+    c2 += uint64_t(m2[i]) + 0x88888888u;
+    k[i + 4] = uint32_t(c1);
+    m2[i + 4] = uint32_t(c2);
+    c1 >>= 32;
+    c2 >>= 32;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; i++) k[i] = m2[i] = 0;
+}
+
 // words of a slot before beta x of its entry
 template <class F>
 constexpr int vt_beta_at() {
@@ -654,35 +677,15 @@ __device__ __forceinline__ void vt_mul_glv(Jz<C>& A, bool& inf, uint32_t* __rest
   constexpr int NL = F::NL;
   constexpr int XW = (NL + 3) / 4 * 4;
   static_assert(vt_beta_at<F>() + XW <= vt_slot<F>(), "beta x inside its slot");
-  static_assert(Glv<C>::BITS <= 126, "the signed nibbles of a half end in 128 bits");
-  reduce_order<C>(k);
-  uint32_t m1[8], m2[8];
+  uint32_t m2[8];
   bool n1, n2;
-  glv_split<C>(k, m1, n1, m2, n2);  // |halves| < 2^BITS for every k < r
+  vt_split<C>(k, m2, n1, n2);
   constexpr Words<NL> beta = Glv<C>::BETA;
 #pragma unroll 1
   for (int d = 0; d < VT_N; d++) {
     uint32_t w[XW] = {};
     vt_pack<F>(w, lz_mul<F>(vt_get_affine<C>(tab + d * vt_slot<F>()).x, lz_of<F>(fp_from<F>(beta))));
     vt_store(tab + d * vt_slot<F>() + vt_beta_at<F>(), w);
-  }
-  // 128-bit signed nibbles, no carry out of the halves; the digits are then
-  // taken from the top of words 4..7
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    m1[i + 4] = m1[i];
-    m2[i + 4] = m2[i];
-    m1[i] = m2[i] = 0;
-  }
-  uint64_t c1 = 0, c2 = 0;
-#pragma unroll
-  for (int i = 4; i < 8; i++) {
-    c1 += uint64_t(m1[i]) + 0x88888888u;
-    c2 += uint64_t(m2[i]) + 0x88888888u;
-    m1[i] = uint32_t(c1);
-    m2[i] = uint32_t(c2);
-    c1 >>= 32;
-    c2 >>= 32;
   }
   inf = true;
   const LzAffine<C> Q = vt_get_affine<C>(tab);
@@ -696,7 +699,7 @@ __device__ __forceinline__ void vt_mul_glv(Jz<C>& A, bool& inf, uint32_t* __rest
     // the two additions as one piece of code
 #pragma unroll 1
     for (int h = 0; h < 2; h++) {
-      const int f = int(h ? take_top<4>(m2) : take_top<4>(m1)) - 8;
+      const int f = int(h ? take_top<4>(m2) : take_top<4>(k)) - 8;
       const int d = (h ? n2 : n1) ? -f : f;
       if (d == 0) continue;
       const uint32_t* sl = tab + ((d < 0 ? -d : d) - 1) * vt_slot<F>();
@@ -711,6 +714,175 @@ __device__ __forceinline__ void vt_mul_glv(Jz<C>& A, bool& inf, uint32_t* __rest
   }
 }
 
+// ---- the same on four lanes per request ------------------------------------------
+// A call of few requests leaves most SIMDs without a wave, and a request's
+// doublings are one chain.  Up to QUAD_MAX requests (four lanes of each then
+// make one wave on every SIMD) the point operations take a quad of lanes each
+// (quad.h); past it every lane has a request of its own.
+// Measured: 256 secp256r1 verifications 1.38 -> 0.90 ms, 3001 BN254 products
+// 0.86 -> 0.68 ms.
+constexpr size_t QUAD_MAX = size_t(1) << 14;
+
+// words per table entry: X, Y, ZZ, ZZZ, then the chain prefix and a flag word
+template <class F>
+constexpr int qvt_coord() {
+  return (F::NL + 1 + 3) / 4 * 4;
+}
+template <class F>
+constexpr int qvt_slot() {
+  return 5 * qvt_coord<F>();
+}
+
+template <class F>
+__device__ __forceinline__ void qvt_store(uint32_t* __restrict__ s, const Lz<F>& a, uint32_t flag = 0) {
+  uint32_t w[qvt_coord<F>()] = {};
+  vt_pack<F>(w, a);
+  w[F::NL] = flag;
+  vt_store(s, w);
+}
+
+template <class F>
+__device__ __forceinline__ Lz<F> qvt_load(const uint32_t* __restrict__ s) {
+  uint32_t w[qvt_coord<F>()];
+  vt_load(s, w);
+  return vt_unpack<F>(w);
+}
+
+// vt_build by a quad: entry d is made across the quad and stored one
+// coordinate per lane; the chain runs over the ZZZ
+template <class C, int WG>
+__device__ __forceinline__ void qvt_build(uint32_t* __restrict__ tab, const Affine<C>& Q, Fp<typename C::F>* s_tot,
+                                          Fp<typename C::F>* s_inv) {
+  using F = typename C::F;
+  constexpr int CWQ = qvt_coord<F>();
+  constexpr int SLOT = qvt_slot<F>();
+  const int q = quad_lane();
+  const Qz<C> B = qz_affine<C>(lz_of<F>(Q.x), lz_of<F>(Q.y));
+  Qz<C> T = B;
+  qz_dbl<C>(T);  // no curve here has a point of order 2
+  bool inf = false;
+  Lz<F> pref = lz_one<F>();
+#pragma unroll 1
+  for (int d = 2; d <= VT_N; d++) {
+    uint32_t* sl = tab + (d - 1) * SLOT;
+    const Lz<F> z = lz_select<F>(inf, lz_one<F>(), quad_perm<F, QUAD_ALL(3)>(T));
+    qvt_store<F>(sl + q * CWQ, q == 3 ? z : T);
+    if (q == 0) qvt_store<F>(sl + 4 * CWQ, pref, inf ? 1u : 0u);
+    pref = lz_mul<F>(pref, z);
+    if (d < VT_N) qz_madd<C>(T, inf, B);
+  }
+  Lz<F> inv = lz_of<F>(wg_batch_inverse<F, WG, 4>(lz_semi<F>(pref), s_tot, s_inv));
+  __threadfence_block();  // the quad's lanes read each other's stores
+#pragma unroll 1
+  for (int d = VT_N; d >= 2; d--) {
+    uint32_t* sl = tab + (d - 1) * SLOT;
+    uint32_t pw[CWQ];
+    vt_load(sl + 4 * CWQ, pw);
+    const Lz<F> mine = qvt_load<F>(sl + q * CWQ);
+    // 1 / ZZZ_d in lane 0 and 1 / (ZZZ_2 ... ZZZ_(d-1)) in lane 1
+    const Lz<F> t = lz_mul<F>(inv, lz_select<F>(q == 0, vt_unpack<F>(pw), quad_perm<F, QUAD_ALL(3)>(mine)));
+    const Lz<F> izzz = quad_perm<F, QUAD_ALL(0)>(t);
+    inv = quad_perm<F, QUAD_ALL(1)>(t);
+    const Lz<F> iz = lz_mul<F>(quad_perm<F, QUAD_ALL(2)>(mine), izzz);  // 1 / Z
+    Lz<F> r = lz_mul<F>(mine, lz_select<F>(q == 0, lz_sqr<F>(iz), izzz));  // x in lane 0, y in lane 1
+    if (pw[F::NL]) r = lz_of<F>(fp_inf_marker<F>());
+    if (q < 2) qvt_store<F>(sl + q * CWQ, r);
+    if constexpr (vt_glv<C>()) {
+      constexpr Words<F::NL> beta = Glv<C>::BETA;
+      const Lz<F> bx = lz_mul<F>(r, lz_of<F>(fp_from<F>(beta)));
+      if (q == 0) qvt_store<F>(sl + 2 * CWQ, bx);
+    }
+  }
+  if (q < 2) qvt_store<F>(tab + q * CWQ, B);
+  if constexpr (vt_glv<C>()) {
+    constexpr Words<F::NL> beta = Glv<C>::BETA;
+    const Lz<F> bx = lz_mul<F>(B, lz_of<F>(fp_from<F>(beta)));
+    if (q == 0) qvt_store<F>(tab + 2 * CWQ, bx);
+  }
+  __threadfence_block();
+}
+
+// A += d Q (d in [-8, 7]), or d phi(Q) where phi
+template <class C>
+__device__ __forceinline__ void qvt_add_digit(Qz<C>& A, bool& inf, const uint32_t* __restrict__ tab, int d, bool phi) {
+  using F = typename C::F;
+  constexpr int CWQ = qvt_coord<F>();
+  if (d == 0) return;
+  const int q = quad_lane();
+  const uint32_t* sl = tab + ((d < 0 ? -d : d) - 1) * qvt_slot<F>();
+  Qz<C> B = q < 2 ? qvt_load<F>(sl + (q == 0 && phi ? 2 : q) * CWQ) : lz_one<F>();
+  if (quad32<QUAD_ALL(0)>(B.w[0]) < 0) return;  // O
+  B = lz_neg_if<F>(B, q == 1 && d < 0);
+  qz_madd<C>(A, inf, B);
+}
+
+// vt_mul and vt_mul_glv by a quad
+template <class C>
+__device__ __forceinline__ void qvt_mul(Qz<C>& A, bool& inf, const uint32_t* __restrict__ tab, uint32_t (&u)[8]) {
+  using F = typename C::F;
+  constexpr int CWQ = qvt_coord<F>();
+  const int q = quad_lane();
+  A = q < 2 ? qvt_load<F>(tab + q * CWQ) : lz_one<F>();
+  if constexpr (vt_glv<C>()) {
+    uint32_t m2[8];
+    bool n1, n2;
+    vt_split<C>(u, m2, n1, n2);
+    inf = true;
+#pragma unroll 1
+    for (int w = 31; w >= 0; w--) {
+#pragma unroll 1
+      for (int k = 0; k < 4; k++) qz_dbl<C>(A);
+#pragma unroll 1
+      for (int h = 0; h < 2; h++) {
+        const int f = int(h ? take_top<4>(m2) : take_top<4>(u)) - 8;
+        qvt_add_digit<C>(A, inf, tab, (h ? n2 : n1) ? -f : f, h != 0);
+      }
+    }
+  } else {
+    inf = !signed_nibbles(u);
+#pragma unroll 1
+    for (int w = 63; w >= 0; w--) {
+#pragma unroll 1
+      for (int k = 0; k < 4; k++) qz_dbl<C>(A);
+      qvt_add_digit<C>(A, inf, tab, int(take_top<4>(u)) - 8, false);
+    }
+  }
+}
+
+// A += k G: each lane sums every fourth window on its own, then the quad adds
+// the four sums
+template <class C, int W>
+__device__ __forceinline__ void qcomb_add(Qz<C>& A, bool& inf, const uint32_t* __restrict__ gcomb,
+                                          const uint32_t (&k)[8]) {
+  Xz<C> P;
+  bool pinf = true;
+  P.X = P.Y = P.ZZ = P.ZZZ = lz_one<typename C::F>();
+  comb_add<C, W>(P, pinf, gcomb, k, quad_lane(), 4);
+  const int fl = pinf ? 1 : 0;
+#pragma unroll 1
+  for (int s = 0; s < 4; s++) {
+    // lane s's point, by rotating the lanes' points one place at each step
+    const Qz<C> B = qz_spread<C, 0>(P);
+    qz_add<C>(A, inf, B, ((quad32<QUAD_ALL(0)>(fl) | (quad32<QUAD_ALL(1)>(fl) << 1) | (quad32<QUAD_ALL(2)>(fl) << 2) |
+                           (quad32<QUAD_ALL(3)>(fl) << 3)) >> s) & 1);
+    xz_map<C>(P, P, [](int32_t v) { return quad32<quad_sel(1, 2, 3, 0)>(v); });
+  }
+}
+
+// A = k G on one lane or on a quad (the sum then in every lane); true if O
+template <class C, int W, int LPR>
+__device__ __forceinline__ bool comb_sum(Xz<C>& A, const uint32_t* __restrict__ gcomb, const uint32_t (&k)[8]) {
+  bool inf = true;
+  if constexpr (LPR == 4) {
+    Qz<C> S = lz_one<typename C::F>();
+    qcomb_add<C, W>(S, inf, gcomb, k);
+    A = qz_gather<C>(S);
+  } else {
+    comb_add<C, W>(A, inf, gcomb, k);
+  }
+  return inf;
+}
+
 // X / ZZ = v for a canonical 256-bit v < p
 template <class C>
 __device__ __forceinline__ bool x_is(const Xz<C>& A, const uint32_t (&v)[8]) {
@@ -718,8 +890,9 @@ __device__ __forceinline__ bool x_is(const Xz<C>& A, const uint32_t (&v)[8]) {
   return lz_is_zero<F>(lz_sub<F>(lz_mul<F>(lz_of<F>(fp_to_mont<F>(fp_from_words<F>(v))), A.ZZ), A.X));
 }
 
-// scratch: VT_N * vt_slot<F>() words per lane of the grid (dead lanes included)
-template <class C, int WG, int W>
+// LPR lanes per request: 1, or 4 (a quad).  scratch: VT_N * vt_slot<F>() words
+// (a quad: qvt_slot) per request of the grid, dead ones included
+template <class C, int WG, int W, int LPR = 1>
 __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) k_verify_xyzz(const uint8_t* __restrict__ hashes,
                                                     const uint32_t* __restrict__ pubkeys,
                                                     const uint32_t* __restrict__ sigs, size_t m,
@@ -729,7 +902,7 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) k_
   using N = typename OrderField<C>::type;
   __shared__ Fp<F> s_tot[WG / 64], s_inv[WG / 64];
   __shared__ Fp<N> n_tot[WG / 64], n_inv[WG / 64];
-  const size_t i = size_t(blockIdx.x) * WG + threadIdx.x;
+  const size_t i = (size_t(blockIdx.x) * WG + threadIdx.x) / LPR;
   const bool live = i < m;
   constexpr Words<8> n32 = N::P32;
   constexpr Words<8> p32 = F::P32;
@@ -738,19 +911,26 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) k_
   bool ok;
   verify_prologue<C, WG>(hashes, pubkeys, sigs, i, live, n_tot, n_inv, rw, u1, u2, Q, ok);
 
-  uint32_t* tab = scratch + i * size_t(VT_N * vt_slot<F>());
-  vt_build<C, WG>(tab, Q, s_tot, s_inv);
-  Xz<C> A;
+  Xz<C> A;  // u2 Q, then u2 Q + u1 G
   bool inf;
-  {  // A = u2 Q
+  if constexpr (LPR == 4) {
+    uint32_t* tab = scratch + i * size_t(VT_N * qvt_slot<F>());
+    qvt_build<C, WG>(tab, Q, s_tot, s_inv);
+    Qz<C> S;
+    qvt_mul<C>(S, inf, tab, u2);
+    qcomb_add<C, W>(S, inf, gcomb, u1);
+    A = qz_gather<C>(S);
+  } else {
+    uint32_t* tab = scratch + i * size_t(VT_N * vt_slot<F>());
+    vt_build<C, WG>(tab, Q, s_tot, s_inv);
     Jz<C> J;
     vt_mul<C>(J, inf, tab, u2);
     A.X = J.X;
     A.Y = J.Y;
     A.ZZ = lz_sqr<F>(J.Z);
     A.ZZZ = lz_mul<F>(J.Z, A.ZZ);
+    comb_add<C, W>(A, inf, gcomb, u1);
   }
-  comb_add<C, W>(A, inf, gcomb, u1);
 
   // ---- R.x mod n == r: R.x is below p < 2n, so R.x = r or R.x = r + n ----
   if (live) {
@@ -768,7 +948,7 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) k_
       if (!eq && cy == 0 && words_lt8(rn, p32.w)) eq = x_is<C>(A, rn);
       good = eq;
     }
-    valid[i] = good ? 1 : 0;
+    if (threadIdx.x % LPR == 0) valid[i] = good ? 1 : 0;
   }
 }
 
@@ -782,7 +962,7 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) k_
 // is summed from the comb table in XYZZ coordinates on the lane,
 // and 1 / ZZ (for R.x = X / ZZ) and k^-1 are one GAS inversion each per
 // workgroup.
-template <class C, int WG, int W>
+template <class C, int WG, int W, int LPR = 1>
 __global__ void __launch_bounds__(WG) k_sign(const uint8_t* __restrict__ hashes, const uint32_t* __restrict__ privkeys,
                                              const uint32_t* __restrict__ nonces, size_t m,
                                              const uint32_t* __restrict__ gcomb, uint32_t* __restrict__ sigs) {
@@ -790,7 +970,7 @@ __global__ void __launch_bounds__(WG) k_sign(const uint8_t* __restrict__ hashes,
   using N = typename OrderField<C>::type;
   __shared__ Fp<F> s_tot[WG / 64], s_inv[WG / 64];
   __shared__ Fp<N> n_tot[WG / 64], n_inv[WG / 64];
-  const size_t i = size_t(blockIdx.x) * WG + threadIdx.x;
+  const size_t i = (size_t(blockIdx.x) * WG + threadIdx.x) / LPR;
   const bool live = i < m;
   constexpr Words<8> n32 = N::P32;
   uint32_t dw[8], kw[8], ew[8];
@@ -814,8 +994,7 @@ __global__ void __launch_bounds__(WG) k_sign(const uint8_t* __restrict__ hashes,
 
   // ---- R = k G from the comb ----
   Xz<C> A;
-  bool inf = true;
-  comb_add<C, W>(A, inf, gcomb, kw);
+  comb_sum<C, W, LPR>(A, gcomb, kw);
   // 0 < k < n, so R != O and ZZ != 0
   const Fp<F> izz = wg_batch_inverse<F, WG, 4>(lz_semi<F>(A.ZZ), s_tot, s_inv);
   uint32_t rw[8];
@@ -837,7 +1016,7 @@ __global__ void __launch_bounds__(WG) k_sign(const uint8_t* __restrict__ hashes,
                             fp_mul<N>(fp_to_mont<N>(fp_from_words<N>(rw)), fp_to_mont<N>(fp_from_words<N>(dw))));
   uint32_t sw[8];
   fp_to_words<N>(fp_from_mont<N>(fp_mul<N>(t, kinv)), sw);
-  if (live) {
+  if (live && threadIdx.x % LPR == 0) {
     const bool good = ok && !words_zero8(rw) && !words_zero8(sw);
 #pragma unroll
     for (int k = 0; k < 8; k++) {
@@ -857,14 +1036,14 @@ __global__ void __launch_bounds__(WG) k_sign(const uint8_t* __restrict__ hashes,
 // in the per-lane verification, then the result's 1 / Z by one GAS inversion
 // per workgroup.  pts are working-form affine points (the infinity
 // marker for O); every k_i is a 256-bit integer, taken as is.
-template <class C, int WG>
+template <class C, int WG, int LPR = 1>
 __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(C::NL > 10 ? 1 : 2))) k_pmul(const uint32_t* __restrict__ pts, const uint32_t* __restrict__ ks,
                                              size_t n, uint32_t* __restrict__ scratch, uint32_t* __restrict__ out,
                                              int out_mont) {
   using F = typename C::F;
   constexpr int PW = affine_words<C>();
   __shared__ Fp<F> s_tot[WG / 64], s_inv[WG / 64];
-  const size_t i = size_t(blockIdx.x) * WG + threadIdx.x;
+  const size_t i = (size_t(blockIdx.x) * WG + threadIdx.x) / LPR;
   const bool live = i < n;
   Affine<C> P;
   uint32_t k[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -879,17 +1058,37 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(C::NL >
     P.x = fp_from<F>(gx);
     P.y = fp_from<F>(gy);
   }
-  uint32_t* tab = scratch + i * size_t(VT_N * vt_slot<F>());
-  vt_build<C, WG>(tab, P, s_tot, s_inv);
-  Jz<C> A;
+  Lz<F> X, Y, iz2, iz3;  // the result is (X iz2, Y iz3)
   bool inf;
-  if constexpr (vt_glv<C>()) vt_mul_glv<C>(A, inf, tab, k);
-  else vt_mul<C>(A, inf, tab, k);
-  inf = inf || pinf;
-  const Lz<F> iz = lz_of<F>(wg_batch_inverse<F, WG>(inf ? fp_one<F>() : lz_semi<F>(A.Z), s_tot, s_inv));
-  const Lz<F> iz2 = lz_sqr<F>(iz);
-  store_lz_affine<C>(lz_mul<F>(A.X, iz2), lz_mul<F>(A.Y, lz_mul<F>(iz, iz2)), inf, live, out + i * 2 * F::N32,
-                     out_mont);
+  if constexpr (LPR == 4) {
+    uint32_t* tab = scratch + i * size_t(VT_N * qvt_slot<F>());
+    qvt_build<C, WG>(tab, P, s_tot, s_inv);
+    Qz<C> S;
+    qvt_mul<C>(S, inf, tab, k);
+    inf = inf || pinf;
+    const Xz<C> A = qz_gather<C>(S);
+    X = A.X;
+    Y = A.Y;
+    // 1 / (ZZ ZZZ) gives both inverses
+    const Lz<F> z = lz_mul<F>(A.ZZ, A.ZZZ);
+    const Lz<F> t = lz_of<F>(wg_batch_inverse<F, WG>(inf ? fp_one<F>() : lz_semi<F>(z), s_tot, s_inv));
+    iz2 = lz_mul<F>(t, A.ZZZ);
+    iz3 = lz_mul<F>(t, A.ZZ);
+  } else {
+    uint32_t* tab = scratch + i * size_t(VT_N * vt_slot<F>());
+    vt_build<C, WG>(tab, P, s_tot, s_inv);
+    Jz<C> A;
+    if constexpr (vt_glv<C>()) vt_mul_glv<C>(A, inf, tab, k);
+    else vt_mul<C>(A, inf, tab, k);
+    inf = inf || pinf;
+    X = A.X;
+    Y = A.Y;
+    const Lz<F> iz = lz_of<F>(wg_batch_inverse<F, WG>(inf ? fp_one<F>() : lz_semi<F>(A.Z), s_tot, s_inv));
+    iz2 = lz_sqr<F>(iz);
+    iz3 = lz_mul<F>(iz, iz2);
+  }
+  store_lz_affine<C>(lz_mul<F>(X, iz2), lz_mul<F>(Y, iz3), inf, live && threadIdx.x % LPR == 0,
+                     out + i * 2 * F::N32, out_mont);
 }
 
 // ---- batched unknown-point multiplication in affine coordinates ------------
@@ -1055,24 +1254,23 @@ __global__ void __launch_bounds__(WG) k_upmul_affine(const uint32_t* __restrict_
 // k_i from the context's comb table (the paper's FPMUL with a precomputed
 // table, Section 2.1), in XYZZ coordinates on the lane, then the affine result
 // by one GAS inversion per workgroup.
-template <class C, int WG, int W>
+template <class C, int WG, int W, int LPR = 1>
 __global__ void __launch_bounds__(WG) k_fixed_base_comb(const uint32_t* __restrict__ ks, size_t n,
                                                         const uint32_t* __restrict__ gcomb, uint32_t* __restrict__ out,
                                                         int out_mont) {
   using F = typename C::F;
   __shared__ Fp<F> s_tot[WG / 64], s_inv[WG / 64];
-  const size_t i = size_t(blockIdx.x) * WG + threadIdx.x;
+  const size_t i = (size_t(blockIdx.x) * WG + threadIdx.x) / LPR;
   const bool active = i < n;
   uint32_t k[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   if (active) load_scalar(ks + 8 * i, k);
   Xz<C> A;
-  bool inf = true;
-  comb_add<C, W>(A, inf, gcomb, k);
+  const bool inf = comb_sum<C, W, LPR>(A, gcomb, k);
   const Lz<F> one = lz_one<F>();
   if (inf) xz_set<C>(A, one, one);
   const Lz<F> t = lz_of<F>(wg_batch_inverse<F, WG>(lz_semi<F>(lz_mul<F>(A.ZZ, A.ZZZ)), s_tot, s_inv));
-  store_lz_affine<C>(lz_mul<F>(A.X, lz_mul<F>(t, A.ZZZ)), lz_mul<F>(A.Y, lz_mul<F>(t, A.ZZ)), inf, active,
-                     out + i * 2 * F::N32, out_mont);
+  store_lz_affine<C>(lz_mul<F>(A.X, lz_mul<F>(t, A.ZZZ)), lz_mul<F>(A.Y, lz_mul<F>(t, A.ZZ)), inf,
+                     active && threadIdx.x % LPR == 0, out + i * 2 * F::N32, out_mont);
 }
 
 }  // namespace eccmi
