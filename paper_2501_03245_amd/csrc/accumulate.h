@@ -27,11 +27,16 @@
 // sort, so that the lanes of a wave end together (buckets of uniform scalars
 // hold 64 +- 8 entries at 2^20 points, and the longest of 64 lanes is 83) and
 // the last waves are short ones.  The partial sums of a cut bucket are added
-// by 1 to 16 lanes (a bucket has few parts, so lanes beyond that idle), or by a
-// workgroup when there are very many.
+// by 1 to 4 lanes, as many as the device has for such buckets; 16 lanes where
+// there are more than four (the few buckets of a skewed top window hold 16 times
+// the entries of the others at 2^16 points, and on one lane each their 17
+// additions outlasted all else: 235 -> 96 us); a workgroup when there
+// are very many.  acuts holds buckets of few parts from its start, of very many
+// from the end of its first half, and the others in its second half.
 #pragma once
 #include "kernels.h"
 #include "lazy.h"
+#include "quad.h"
 
 namespace eccmi {
 
@@ -39,6 +44,8 @@ constexpr uint32_t ACC_BINS = 1024;       // item lengths told apart by the sort
 constexpr uint32_t ACC_MIN_CAP = 4;
 constexpr int ACC_MERGE_LG_LANES = 4;     // at most 16 lanes add the parts of a cut bucket
 constexpr uint32_t ACC_MERGE_TARGET = 65536;  // lanes the merge spreads over (one wave per SIMD)
+constexpr uint32_t ACC_QUAD_CUTS = 4096;      // bound on the cut buckets up to which a quad takes the place of a lane
+constexpr uint32_t ACC_MERGE_FEW = 4;     // parts up to which the lanes follow the number of such buckets
 constexpr uint32_t ACC_MERGE_MAX = 256;   // parts beyond which a workgroup adds them
 constexpr int ACC_PLAN_WG = 1024;
 constexpr int ACC_WG = 256;
@@ -48,8 +55,9 @@ constexpr int ACC_MERGE_WG = 256;
 struct AccMeta {
   uint32_t items;       // work items
   uint32_t extra;       // parts beyond the first of their bucket
-  uint32_t cut;         // cut buckets of at most ACC_MERGE_MAX parts
-  uint32_t cut_big;     // cut buckets of more
+  uint32_t cut;         // cut buckets of at most ACC_MERGE_FEW parts
+  uint32_t cut_mid;     // of more, up to ACC_MERGE_MAX
+  uint32_t cut_big;     // of more than that
   uint32_t hist[ACC_BINS];  // items by bin
   uint32_t cursor[ACC_BINS];
 };
@@ -126,8 +134,10 @@ static __global__ void __launch_bounds__(ACC_PLAN_WG) k_acc_items(const uint32_t
     uint32_t extra = 0;
     if (parts > 1) {
       extra = atomicAdd(&meta->extra, parts - 1);
-      if (parts <= ACC_MERGE_MAX) cuts[atomicAdd(&meta->cut, 1u)] = AccCut{b, parts, extra};
-      else cuts[cut_cap - 1 - atomicAdd(&meta->cut_big, 1u)] = AccCut{b, parts, extra};
+      const AccCut cut{b, parts, extra};
+      if (parts <= ACC_MERGE_FEW) cuts[atomicAdd(&meta->cut, 1u)] = cut;
+      else if (parts <= ACC_MERGE_MAX) cuts[cut_cap + atomicAdd(&meta->cut_mid, 1u)] = cut;
+      else cuts[cut_cap - 1 - atomicAdd(&meta->cut_big, 1u)] = cut;
     }
     if (parts <= 64) {
       for (uint32_t j = 0; j < parts; j++) put(at, off, b, n, parts, extra, j);
@@ -228,28 +238,90 @@ __device__ __forceinline__ void acc_merge(Xz<C>& A, bool& inf, const AccCut& cut
   }
 }
 
+// log2 of the lanes (or quads) that add the parts of each of n cut buckets of
+// few parts: as many as `target` allows, since a lane's additions form a chain
+__device__ __forceinline__ int acc_merge_lanes(uint32_t n, uint32_t target) {
+  int lg = 0;
+  while ((2u << lg) <= ACC_MERGE_FEW && (n << (lg + 1)) <= target) lg++;
+  return lg;
+}
+
 template <class C>
 __global__ void __launch_bounds__(ACC_MERGE_WG) __attribute__((amdgpu_waves_per_eu(2, 2))) k_acc_merge(
-    const AccMeta* __restrict__ meta, const AccCut* __restrict__ cuts, uint32_t B, uint32_t* __restrict__ psum) {
-  const uint32_t n = meta->cut;
-  if (n == 0) return;
-  // lanes per bucket: as many as leave one wave on each SIMD, since a lane's
-  // additions form a chain; one lane each where there are buckets enough
-  int lgG = 0;
-  while (lgG < ACC_MERGE_LG_LANES && (n << (lgG + 1)) <= ACC_MERGE_TARGET) lgG++;
-  const uint32_t G = 1u << lgG;
-  const uint32_t l = threadIdx.x & (G - 1);
-  // the wave's cut buckets; the loop's bounds are wave-uniform
-  for (uint32_t w = (blockIdx.x * ACC_MERGE_WG + threadIdx.x) / 64; (w << (6 - lgG)) < n;
-       w += gridDim.x * (ACC_MERGE_WG / 64)) {
-    const uint32_t i = (w << (6 - lgG)) + ((threadIdx.x & 63u) >> lgG);
-    const AccCut cut = i < n ? cuts[i] : AccCut{0u, 0u, 0u};
-    int tree = 0;  // levels the widest of the wave's buckets needs
-    while (tree < lgG && __ballot((1u << tree) < cut.parts) != 0) tree++;
-    Xz<C> A;
-    bool inf;
-    acc_merge<C>(A, inf, cut, l, G, B, psum, tree);
-    if (i < n && l == 0) xz_store<C>(psum + size_t(cut.bucket) * xyzz_words<C>(), A, inf);
+    const AccMeta* __restrict__ meta, const AccCut* __restrict__ cuts, uint32_t cut_cap, uint32_t B,
+    uint32_t* __restrict__ psum) {
+  const uint32_t waves = gridDim.x * (ACC_MERGE_WG / 64);
+  const uint32_t wave = (blockIdx.x * ACC_MERGE_WG + threadIdx.x) / 64;
+  // the buckets of more parts first, from the last wave on, then the others
+#pragma unroll 1
+  for (int pass = 0; pass < 2; pass++) {
+    const uint32_t n = pass == 0 ? meta->cut_mid : meta->cut;
+    const AccCut* list = pass == 0 ? cuts + cut_cap : cuts;
+    const int lgG = pass == 0 ? ACC_MERGE_LG_LANES : acc_merge_lanes(n, ACC_MERGE_TARGET);
+    const uint32_t G = 1u << lgG;
+    const uint32_t l = threadIdx.x & (G - 1);
+    // the wave's cut buckets; the loop's bounds are wave-uniform
+    for (uint32_t w = pass == 0 ? waves - 1 - wave : wave; (w << (6 - lgG)) < n; w += waves) {
+      const uint32_t i = (w << (6 - lgG)) + ((threadIdx.x & 63u) >> lgG);
+      const AccCut cut = i < n ? list[i] : AccCut{0u, 0u, 0u};
+      int tree = 0;  // levels the widest of the wave's buckets needs
+      while (tree < lgG && __ballot((1u << tree) < cut.parts) != 0) tree++;
+      Xz<C> A;
+      bool inf;
+      acc_merge<C>(A, inf, cut, l, G, B, psum, tree);
+      if (i < n && l == 0) xz_store<C>(psum + size_t(cut.bucket) * xyzz_words<C>(), A, inf);
+    }
+  }
+}
+
+// the same with a quad of lanes in the place of a lane, for calls of at most
+// ACC_QUAD_CUTS cut buckets (1021 BLS12-381 points: 74 -> 31 us; 4096 BN254
+// points, with 6,656 buckets, take longer: 60 -> 95 us)
+template <class C>
+__global__ void __launch_bounds__(ACC_MERGE_WG) k_acc_merge_quad(const AccMeta* __restrict__ meta,
+                                                                 const AccCut* __restrict__ cuts, uint32_t cut_cap,
+                                                                 uint32_t B, uint32_t* __restrict__ psum) {
+  constexpr int XW = xyzz_words<C>();
+  const uint32_t waves = gridDim.x * (ACC_MERGE_WG / 64);
+  const uint32_t wave = (blockIdx.x * ACC_MERGE_WG + threadIdx.x) / 64;
+  const uint32_t t = (threadIdx.x & 63u) >> 2;  // quad in its wave
+#pragma unroll 1
+  for (int pass = 0; pass < 2; pass++) {
+    const uint32_t n = pass == 0 ? meta->cut_mid : meta->cut;
+    const AccCut* list = pass == 0 ? cuts + cut_cap : cuts;
+    const int lgG = pass == 0 ? 4 : acc_merge_lanes(n, ACC_MERGE_TARGET / 4);  // quads per bucket
+    const uint32_t G = 1u << lgG;
+    const uint32_t l = t & (G - 1);
+    for (uint32_t w = pass == 0 ? waves - 1 - wave : wave; (w << (4 - lgG)) < n; w += waves) {
+      const uint32_t i = (w << (4 - lgG)) + (t >> lgG);
+      const AccCut cut = i < n ? list[i] : AccCut{0u, 0u, 0u};
+      int tree = 0;
+      while (tree < lgG && __ballot((1u << tree) < cut.parts) != 0) tree++;
+      const uint32_t mine = l < cut.parts ? (cut.parts - l + G - 1) / G : 0u;
+      uint32_t most = mine;
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) most = max(most, uint32_t(__shfl_xor(int(most), d, 64)));
+      Qz<C> A = lz_one<typename C::F>();
+      bool inf = true;
+#pragma unroll 1
+      for (uint32_t st = 0; st < most + uint32_t(tree); st++) {
+        Qz<C> Bp;
+        bool binf = true;
+        if (st < most) {
+          if (st < mine) {
+            const uint32_t j = l + st * G;
+            qz_load<C>(psum + size_t(j == 0 ? cut.bucket : B + cut.extra + j - 1) * XW, Bp, binf);
+          }
+        } else {
+          const int off = 1 << (tree - 1 - int(st - most));
+#pragma unroll
+          for (int k = 0; k < C::F::NL; k++) Bp.w[k] = __shfl_down(A.w[k], 4 * off, 64);
+          binf = __shfl_down(int(inf), 4 * off, 64) != 0 || l + uint32_t(off) >= G;
+        }
+        qz_add<C>(A, inf, Bp, binf);
+      }
+      if (i < n && l == 0) qz_store<C>(psum + size_t(cut.bucket) * XW, A, inf);
+    }
   }
 }
 
@@ -394,6 +466,102 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const XYZZ<C> Y = xz_to_xyzz<C>(S, sinf);
     if (!big) xyzz_store<C>(winsum + size_t(wv.job + slot) * XW, Y);
     else xyzz_store<C>(segY + size_t(jb.seg_base + wv.g) * XW, Y);
+  }
+}
+
+// The same with a quad of lanes in the place of a lane: a workgroup of 256 is
+// one level-A wave of the plan, and its 64 quads exchange points through LDS.
+// Taken while the quads make at most two waves per SIMD, since a chain of
+// about 2 L + 13 + log2 L point operations bounds the phase there: BLS12-381,
+// 1021 points 220 -> 117 us, 2^16 points 235 -> 178 us (1.2 waves per SIMD);
+// BN254, 4096 points 107 -> 66 us.
+// Past that the quad's extra moves cost more than they save.
+constexpr int REDUCE_QUAD_WG = 256;
+
+template <class C>
+__global__ void __launch_bounds__(REDUCE_QUAD_WG) k_reduce_a_quad(
+    const uint32_t* __restrict__ counts, const uint32_t* __restrict__ psum, const RedJob* __restrict__ jobs,
+    const RedWave* __restrict__ waves, uint32_t* __restrict__ segU, uint32_t* __restrict__ segY,
+    uint32_t* __restrict__ winsum) {
+  using F = typename C::F;
+  constexpr int XW = xyzz_words<C>();
+  constexpr int NL = F::NL;
+  __shared__ int32_t s_pt[NL * REDUCE_QUAD_WG];
+  __shared__ int32_t s_inf[REDUCE_QUAD_WG / 4];
+  const RedWave wv = waves[blockIdx.x];
+  const int lgS = int(wv.lgS);
+  const uint32_t quad = threadIdx.x >> 2;
+  const int q = quad_lane();
+  const uint32_t slot = quad >> lgS;             // job slot
+  const uint32_t t = quad & ((1u << lgS) - 1u);  // quad inside the segment
+  const bool active = slot < wv.njobs;
+  const RedJob jb = jobs[wv.job + (active ? slot : 0u)];
+  const int lgL = int(jb.lgD) - int(jb.lgLam);
+  const uint32_t L = 1u << lgL;
+  const uint32_t first = jb.bucket + ((wv.g << 6) + t) * L;
+  // the point of quad `from` of this workgroup (every thread takes part)
+  auto exchange = [&](const Qz<C>& a, bool inf, uint32_t from, bool valid, Qz<C>& b, bool& binf)
+                      __attribute__((always_inline)) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NL; i++) s_pt[i * REDUCE_QUAD_WG + threadIdx.x] = a.w[i];
+    if (q == 0) s_inf[quad] = inf ? 1 : 0;
+    __syncthreads();
+    const uint32_t f = valid ? from : quad;
+#pragma unroll
+    for (int i = 0; i < NL; i++) b.w[i] = s_pt[i * REDUCE_QUAD_WG + f * 4 + q];
+    binf = !valid || s_inf[f] != 0;
+  };
+  auto put = [&](uint32_t* p, const Qz<C>& a, bool inf) __attribute__((always_inline)) {
+    // the semi-reduced form of point.h, one coordinate per lane
+    Fp<F> r = lz_semi<F>(lz_mul<F>(a, lz_one<F>()));
+    if (inf) r = q < 2 ? fp_one<F>() : fp_zero<F>();
+    fp_store<F>(p + q * F::CW, r);
+  };
+  const bool big = jb.lgLam > 6;
+  Qz<C> S = lz_one<F>(), T = S;
+  bool sinf = true, tinf = true;
+  // one loop, so that the addition appears once: the running sums (S += B_k,
+  // T += S), the suffix scan, the addition of T, the butterfly
+  const int n_run = int(2 * L), n_scan = n_run + lgS, n_t = n_scan + 1, n_all = n_t + lgS;
+#pragma unroll 1
+  for (int st = 0; st < n_all; st++) {
+    Qz<C> b = S;
+    bool binf = sinf;
+    const bool second = st < n_run && (st & 1);
+    if (second) {
+      S = T;
+      sinf = tinf;
+    } else if (st < n_run) {
+      const uint32_t k = first + L - 1 - uint32_t(st) / 2;
+      binf = true;
+      if (active && counts[k]) qz_load<C>(psum + size_t(k) * XW, b, binf);
+    } else if (st < n_scan) {
+      const uint32_t off = 1u << (st - n_run);
+      exchange(S, sinf, quad + off, t + off < (1u << lgS), b, binf);
+    } else if (st < n_t) {
+      if (active && t == 0 && big) put(segU + size_t(jb.seg_base + wv.g) * XW, S, sinf);  // the segment total
+#pragma unroll 1
+      for (int i = 0; i < lgL; i++) qz_dbl<C>(S);
+      sinf = sinf || t < 1;
+      b = T;
+      binf = tinf;
+    } else {
+      exchange(S, sinf, quad ^ (1u << (lgS - 1 - (st - n_t))), true, b, binf);
+    }
+    const Qz<C> keep = b;
+    const bool kinf = binf;
+    qz_add<C>(S, sinf, b, binf);
+    if (second) {
+      T = S;
+      tinf = sinf;
+      S = keep;
+      sinf = kinf;
+    }
+  }
+  if (active && t == 0) {
+    if (!big) put(winsum + size_t(wv.job + slot) * XW, S, sinf);
+    else put(segY + size_t(jb.seg_base + wv.g) * XW, S, sinf);
   }
 }
 

@@ -428,7 +428,7 @@ ecc_status reserve_msm(ecc_ctx* ctx, const Geometry& g, uint32_t lanes_max) {
     const size_t extra = acc_extra(ctx, g.E);
     ECC_TRY(ensure(ctx, ctx->psum, (g.B + extra) * XW * 4));
     ECC_TRY(ensure(ctx, ctx->aitems, (std::min(g.B, g.E) + extra) * sizeof(AccItem)));
-    ECC_TRY(ensure(ctx, ctx->acuts, extra * sizeof(AccCut)));
+    ECC_TRY(ensure(ctx, ctx->acuts, 2 * extra * sizeof(AccCut)));
     ECC_TRY(ensure(ctx, ctx->ameta, sizeof(AccMeta)));
   } else {
     ECC_TRY(ensure(ctx, ctx->slots, g.slot_cap * PW * 4));
@@ -485,8 +485,14 @@ ecc_status enqueue_direct(ecc_ctx* ctx, const Geometry& g, hipStream_t st, bool 
   *nr = 1;
   if (g.max_n > cap) {  // no bucket holds more entries than its MSM has points
     if (prof) ECC_TRY(record(ctx, 4, st));
-    const uint32_t blocks = std::min<uint32_t>(ceil_div(extra << ACC_MERGE_LG_LANES, ACC_MERGE_WG), 1024u);
-    k_acc_merge<C><<<blocks, ACC_MERGE_WG, 0, st>>>(meta, P<AccCut>(ctx->acuts), B, psum);
+    const size_t cuts = std::min<size_t>(B, extra);
+    if (cuts <= ACC_QUAD_CUTS) {
+      const uint32_t blocks = std::min<uint32_t>(ceil_div(cuts << (ACC_MERGE_LG_LANES + 2), ACC_MERGE_WG), 1024u);
+      k_acc_merge_quad<C><<<blocks, ACC_MERGE_WG, 0, st>>>(meta, P<AccCut>(ctx->acuts), uint32_t(extra), B, psum);
+    } else {
+      const uint32_t blocks = std::min<uint32_t>(ceil_div(cuts << ACC_MERGE_LG_LANES, ACC_MERGE_WG), 1024u);
+      k_acc_merge<C><<<blocks, ACC_MERGE_WG, 0, st>>>(meta, P<AccCut>(ctx->acuts), uint32_t(extra), B, psum);
+    }
     HIP_TRY(hipGetLastError());
     if (g.max_n > uint64_t(cap) * ACC_MERGE_MAX) {
       k_acc_merge_big<C><<<256, ACC_MERGE_WG, 0, st>>>(meta, P<AccCut>(ctx->acuts), uint32_t(extra), B, psum);
@@ -495,9 +501,15 @@ ecc_status enqueue_direct(ecc_ctx* ctx, const Geometry& g, hipStream_t st, bool 
     if (prof) ECC_TRY(record(ctx, 5, st));
     *finished = true;
   }
-  k_reduce_a_xz<C, REDUCE_WG><<<unsigned(ceil_div(g.waves.size() * 64, REDUCE_WG)), REDUCE_WG, 0, st>>>(
-      counts, psum, GP<RedJob>(ctx, g.off_jobs), GP<RedWave>(ctx, g.off_waves), uint32_t(g.waves.size()),
-      P<uint32_t>(ctx->segS), P<uint32_t>(ctx->segT), P<uint32_t>(ctx->winsum));
+  if (g.waves.size() <= 2 * size_t(ctx->cu_count)) {
+    k_reduce_a_quad<C><<<unsigned(g.waves.size()), REDUCE_QUAD_WG, 0, st>>>(
+        counts, psum, GP<RedJob>(ctx, g.off_jobs), GP<RedWave>(ctx, g.off_waves), P<uint32_t>(ctx->segS),
+        P<uint32_t>(ctx->segT), P<uint32_t>(ctx->winsum));
+  } else {
+    k_reduce_a_xz<C, REDUCE_WG><<<unsigned(ceil_div(g.waves.size() * 64, REDUCE_WG)), REDUCE_WG, 0, st>>>(
+        counts, psum, GP<RedJob>(ctx, g.off_jobs), GP<RedWave>(ctx, g.off_waves), uint32_t(g.waves.size()),
+        P<uint32_t>(ctx->segS), P<uint32_t>(ctx->segT), P<uint32_t>(ctx->winsum));
+  }
   HIP_TRY(hipGetLastError());
   return ECC_OK;
 }

@@ -205,4 +205,19 @@ __device__ __forceinline__ Qz<C> qz_spread(const Xz<C>& P) {
   return r;
 }
 
+// a point stored by xz_store, one coordinate per lane, and back
+template <class C>
+__device__ __forceinline__ void qz_load(const uint32_t* __restrict__ p, Qz<C>& A, bool& inf) {
+  using F = typename C::F;
+  A = lz_load<F>(p + quad_lane() * F::CW);
+  inf = quad32<QUAD_ALL(0)>(A.w[0]) < 0;
+}
+template <class C>
+__device__ __forceinline__ void qz_store(uint32_t* __restrict__ p, const Qz<C>& A, bool inf) {
+  using F = typename C::F;
+  Lz<F> a = A;
+  if (inf && quad_lane() == 0) a.w[0] = -1;
+  lz_store<F>(p + quad_lane() * F::CW, a);
+}
+
 }  // namespace eccmi
