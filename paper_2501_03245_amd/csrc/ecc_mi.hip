@@ -77,12 +77,6 @@ size_t scan_tmp_words(size_t n) {
   return w + 16;
 }
 
-// Window width for an MSM of n points when the caller gives none.  The cost
-// model weighs the W (n + alpha D) bucket work of W = ceil((bits + 1) / c)
-// windows of D = 2^(c-1) buckets: each point is added once per window, and
-// the reduction costs about alpha batch additions per bucket (two chained
-// XYZZ additions, each about 2.5 batch additions' worth of products).  A
-// tuned table from ecc_tune replaces the rule where one exists.
 // bound on the half-scalars of the endomorphism split (0: no split on this curve)
 template <class C>
 constexpr int glv_bits_of() {
@@ -90,14 +84,35 @@ constexpr int glv_bits_of() {
   else return 0;
 }
 
-int model_window(int bits, size_t n, double alpha) {
+// Window width when the caller gives none and the context is not tuned.
+//
+// One MSM alone is bound by chains, not by its total work: the additions of its
+// longest buckets and of their parts.  Scalars of 128 or 256 bits leave the
+// top window of most widths only a few bits, so that a handful of buckets hold
+// many times the entries of the others; 8 and 16 divide them evenly.  Swept
+// over widths 4 to 16 and 2^8 to 2^20 points, one of the two was fastest at
+// every size, 8 up to 2^15 points (after the split, 2^16) and 16 from the next
+// power of two on: 2^14 BLS12-381 points 1.04 ms (11, by the model below)
+// -> 0.75 ms, 2^18 points 1.74 ms (13) -> 1.43 ms, 2^12 BN254 points 0.52 ms
+// (10) -> 0.48 ms; the line lies between 2^16 and 2^17 points.
+constexpr size_t SINGLE_WIDE_POINTS = 3 << 15;
+int single_window(size_t n_eff) { return n_eff < SINGLE_WIDE_POINTS ? 8 : 16; }
+
+// A batch is bound by its total work: W = ceil((bits + 1) / c) windows of n
+// additions, D = 2^(c-1) buckets whose two XYZZ additions cost 28 products
+// against the 10 of an entry's, and a share of the scans and the combination.
+// The constants give the measured best width of batches of 2^2 .. 2^14 points
+// per MSM (4, 4, 5, 6, 8, 8, 8, 10, 10, 11 for 2^2, 2^4, 2^6, 2^8 .. 2^14);
+// with 5 D and no constant, 8192 MSMs of 4 points took 8.2 ms instead of 6.0
+// and 2048 of 512 points 9.2 ms instead of 8.2.
+int batch_window(int bits, size_t n) {
   int best = 2;
   double best_cost = 1e300;
   // up to 16: the widest window whose buckets the LDS grouping and the
   // reduction waves handle without long per-lane chains (wider only if tuned)
   for (int c = 2; c <= 16; c++) {
     double W = double((bits + 1 + c - 1) / c);
-    double cost = W * (double(n) + alpha * double(1u << (c - 1)));
+    double cost = W * (double(n) + 3.5 * double(1u << (c - 1)) + 40.0);
     if (cost < best_cost) {
       best_cost = cost;
       best = c;
@@ -108,11 +123,11 @@ int model_window(int bits, size_t n, double alpha) {
 
 // n_in: points given by the caller (the tuned table's index); bits and n_eff:
 // scalar bits and points of the bucket work (2 n_in points of half-length
-// scalars after the endomorphism split)
-int default_window(ecc_ctx* ctx, int curve, int bits, size_t n_in, size_t n_eff) {
+// scalars after the endomorphism split); single: the call's only MSM
+int default_window(ecc_ctx* ctx, int curve, int bits, size_t n_in, size_t n_eff, bool single) {
   int lg = bit_length(n_in ? n_in : 1) - 1;
   if (lg < 32 && ctx->tuned[curve][lg] > 0) return ctx->tuned[curve][lg];
-  return model_window(bits, n_eff, 5.0);
+  return single ? single_window(n_eff) : batch_window(bits, n_eff);
 }
 
 // Launch geometry of a batch of MSMs (a single MSM is a batch of one).
@@ -164,7 +179,7 @@ ecc_status build_geometry(ecc_ctx* ctx, int curve, int bits, const uint64_t* siz
       // top window over the 128-bit halves would hold only a few bits of every
       // scalar and pile most entries into a handful of buckets
       if (sizes[0] > 0 && sizes[0] <= GLV_MAX_POINTS) {
-        const int c = c_fixed ? c_fixed : default_window(ctx, curve, glv_bits, sizes[0], 2 * sizes[0]);
+        const int c = c_fixed ? c_fixed : default_window(ctx, curve, glv_bits, sizes[0], 2 * sizes[0], true);
         g.glv = c <= RADIX_SORT_MAX_C;
       }
     } else {
@@ -179,7 +194,7 @@ ecc_status build_geometry(ecc_ctx* ctx, int curve, int bits, const uint64_t* siz
     MsmDesc& d = g.msms[i];
     d.first = uint32_t(g.glv_batch ? 2 * first : first);
     d.n = uint32_t(n);
-    int c = c_fixed ? c_fixed : default_window(ctx, curve, sbits, n_in, n);
+    int c = c_fixed ? c_fixed : default_window(ctx, curve, sbits, n_in, n, m == 1);
     d.c = uint32_t(c);
     d.W = n ? uint32_t((sbits + 1 + c - 1) / c) : 0u;
     d.bucket_base = uint32_t(g.B);
@@ -1047,7 +1062,7 @@ ecc_status tune_impl(ecc_ctx* ctx, int lg_lo, int lg_hi, int reps) {
     const uint64_t* scal = static_cast<const uint64_t*>(sb.p);
     uint64_t* out = static_cast<uint64_t*>(ob.p);
     uint8_t* inf = reinterpret_cast<uint8_t*>(out + IOW / 2);
-    const int c0 = glv_bits_of<C>() ? model_window(glv_bits_of<C>(), 2 * n, 5.0) : model_window(C::SCALAR_BITS, n, 5.0);
+    const int c0 = single_window(glv_bits_of<C>() ? 2 * n : n);
     int best_c = c0;
     double best = 1e300;
     ctx->kmin_override = KMIN;
@@ -1293,8 +1308,8 @@ ecc_status ecc_tuned_params(ecc_ctx* ctx, ecc_curve curve, size_t n, int* window
   if (curve != ECC_BN254_G1 && curve != ECC_BLS12_381_G1) return fail(ctx, ECC_ERR_ARG, "not an MSM curve");
   const int bits = curve == ECC_BN254_G1 ? BN254::SCALAR_BITS : BLS12_381::SCALAR_BITS;
   const int gb = curve == ECC_BN254_G1 ? glv_bits_of<BN254>() : glv_bits_of<BLS12_381>();
-  *window_c = default_window(ctx, curve, gb, n, 2 * n);
-  if (n == 0 || n > GLV_MAX_POINTS || *window_c > RADIX_SORT_MAX_C) *window_c = default_window(ctx, curve, bits, n, n);
+  *window_c = default_window(ctx, curve, gb, n, 2 * n, true);
+  if (n == 0 || n > GLV_MAX_POINTS || *window_c > RADIX_SORT_MAX_C) *window_c = default_window(ctx, curve, bits, n, n, true);
   int lg = bit_length(n ? n : 1) - 1;
   *adds_per_lane = (lg < 32 && ctx->tuned_kmin[curve][lg] > 0) ? ctx->tuned_kmin[curve][lg] : KMIN;
   return ECC_OK;
