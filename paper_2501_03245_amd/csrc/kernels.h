@@ -2389,8 +2389,8 @@ __global__ void k_test_fp_mul(const uint32_t* __restrict__ a, const uint32_t* __
 // op 0: a b, op 1: a - b, op 2: (3a)(a + b) - 2b, and the differences of the
 // point formulas on product outputs (the widest operands lp_sub takes):
 // op 3: 3(ab) - a^2, op 4: (3 b^2 + ab) - a^2, op 5: a^2 - (ab + 2 b^2);
-// a Y coordinate left unreduced (lp_sub_y): op 6: (2(ab - a^2))^2 (the
-// doubling's first product), op 7: ab - a^2 reduced as a point store does
+// a Y coordinate: op 6: (2(ab - a^2))^2 (the doubling's first product), op 7:
+// ab - a^2 alone
 template <class C>
 __global__ void __launch_bounds__(64) k_test_lane_field(const uint32_t* __restrict__ a, const uint32_t* __restrict__ b,
                                                         uint32_t* __restrict__ r, size_t n, int op) {
@@ -2415,20 +2415,20 @@ __global__ void __launch_bounds__(64) k_test_lane_field(const uint32_t* __restri
   if (op == 0) {
     z = lp_mul<F>(xa, yb, k);
   } else if (op == 1) {
-    z = lp_sub<F>(xa, yb, k);
+    z = lp_sub<F>(xa, yb);
   } else if (op == 2) {
     const uint32_t m = lp_carry32<F>(xa + xa + xa);
-    z = lp_sub<F>(lp_mul<F>(m, xa + yb, k), yb + yb, k);
+    z = lp_sub<F>(lp_mul<F>(m, xa + yb, k), yb + yb);
   } else {
     const uint32_t ab = lp_mul<F>(xa, yb, k), aa = lp_mul<F>(xa, xa, k), bb = lp_mul<F>(yb, yb, k);
-    const uint32_t y = lp_sub_y<F>(ab, aa, k);
-    if (op == 3) z = lp_sub<F>(ab + ab + ab, aa, k);
-    else if (op == 4) z = lp_sub<F>(lp_carry32<F>(bb + bb + bb + ab), aa, k);
-    else if (op == 5) z = lp_sub<F>(aa, lp_carry32<F>(ab + bb + bb), k);
-    else if (op == 6) z = lp_mul<F>(y + y, y + y, k);
-    else z = lp_reduce<F>(y, k);
+    const uint32_t y = lp_sub<F>(ab, aa);
+    if (op == 3) z = lp_sub<F>(ab + ab + ab, aa);
+    else if (op == 4) z = lp_sub<F>(lp_carry32<F>(bb + bb + bb), aa - ab);
+    else if (op == 5) z = lp_sub<F>(aa - ab, bb + bb);
+    else if (op == 6) z = lp_mul<F>(lp_carry32_if29<F>(y + y), lp_carry32_if29<F>(y + y), k);
+    else z = y;
   }
-  z = lp_canonical<F>(z, k);
+  z = lp_canonical<F>(lp_fix<F>(z, k), k);
   Fp<F> o;
 #pragma unroll
   for (int i = 0; i < F::NL; i++) o.w[i] = uint32_t(__shfl(int(z), int(threadIdx.x & 48u) + i, 64));

@@ -12,29 +12,39 @@
 //
 // Product (Section 2.2, Algorithm 2 with D = 2^B).  Lane j accumulates the
 // product columns j and j + 16 in two 64-bit registers: for i = 0..NL-1 the
-// limb a_i is broadcast to the row and b is rotated by i lanes, so that lane
-// j multiplies a_i by b_{(j - i) mod 16}, which belongs to column j when
-// j >= i and to column j + 16 otherwise.  The reduction then walks the
-// columns i = 0..NL-1 in order: the broadcast column value plus the carry out
-// of column i - 1 gives M_i = C_i q_inv mod 2^B; M_i q is added at columns
-// i + m through a per-lane table of q's limbs rotated by i; the carry out of
-// column i stays in a register.  Columns NL..2NL-1, rotated back to lanes
+// limb a_i is broadcast to the row and multiplied by b shifted up by i lanes
+// (column j: b_{j-i}, 0 below) and by b shifted down by 16 - i (column j + 16:
+// b_{j-i+16}, 0 past its last limb; nothing is left of it for i <= 16 - NL).
+// The reduction then walks the columns i = 0..NL-1 in order: the broadcast
+// column value plus the carry out of column i - 1 gives M_i = C_i q_inv mod 2^B;
+// M_i q is added at columns i + m through a per-lane table of q's limbs shifted
+// by i; the carry out of column i stays in a register.  Columns NL..2NL-1, rotated back to lanes
 // 0..NL-1, plus the last carry are the result, brought to small limbs by two
 // carry passes.
 //
+// Limbs are signed words (two's complement in uint32_t), as in lazy.h: a
+// difference is one subtraction and one carry pass, with no multiple of p, no
+// quotient and no wait for the last carry; values stay small against R
+// (R / p = 169 on BN254, 2^11 on BLS12-381) until a result is stored.
 // Value conventions:
-//   lp_mul inputs : limbs < 2^30 and a b < 36 p^2 (so that every 64-bit column
-//                   and the Montgomery bound (a b + M q) / R < 2p hold for
-//                   BN254, where R / p ~ 170, and BLS12-381, R / p ~ 2^11);
-//   lp_mul output : limbs < 2^B + 2^9 below the top one, value < 2p;
-//   lp_sub output : limbs <= 2^B below the top one, value < 2p (a - b + 8p,
-//                   then the quotient by p estimated from the top limb is
-//                   subtracted); lp_sub takes a < 8p with limbs below the
-//                   top one < 4 2^B and b < 6p with limbs < 3 2^B - 3;
-//   lp_canonical  : limbs < 2^B, value < p (the canonical form of field.h);
-//   LpPoint Y     : as an lp_sub output, or (where lp_lazy_y holds) below 10p
-//                   with limbs < 2^B + 16 (lp_sub_y).  The point formulas
-//                   multiply it at most as (2Y)^2 < 400 p^2 and Y W < 20 p^2.
+//   lp_mul inputs : a b < 36 p^2 in magnitude; limbs below the top one within
+//                   2^B + 2^9, or one operand's within 2 2^B, and where B is
+//                   28 both operands' within 2 2^B (then every signed 64-bit
+//                   column holds);
+//   lp_mul output : limbs within 2^B + 2^9 below the signed top one, value in
+//                   (-p / 4, 5 p / 4);
+//   lp_sub output : limbs in [-8, 2^B + 8) below the top one (the lowest in
+//                   [0, 2^B)), value a - b; operands' limbs within 3 2^B + 2^11;
+//   lp_fix        : value in (-6p, 8p), limbs as above -> value < 2p, limbs in [0, 2^B];
+//   lp_canonical  : limbs < 2^B, value < p (the canonical form of field.h), from
+//                   lp_fix's output.
+// In a doubling of XYZZ coordinates below 4p in magnitude the operands reach 3,
+// 4 and 5p and the products 15 p^2; in an addition 5p and 16 p^2.
+// The chain is bound by the instructions of its one wave.  A difference that was
+// brought below 2p took 62 instructions, this one 8; with the shorter shifts of
+// the product (271 instructions, 290 before) the window combination takes
+// 186 us on BN254 (236 before) and 255 us on BLS12-381 (290), and 342 us for 512
+// MSMs (487).
 #pragma once
 #include <type_traits>
 
@@ -62,6 +72,7 @@ template <int CTRL>
 __device__ __forceinline__ uint64_t dpp64(uint64_t v) {
   return uint64_t(dpp32<CTRL>(uint32_t(v))) | (uint64_t(dpp32<CTRL>(uint32_t(v >> 32))) << 32);
 }
+constexpr int DPP_ROW_SHL(int n) { return 0x100 + n; }    // lane j <- lane j + n (0 above)
 constexpr int DPP_ROW_SHR(int n) { return 0x110 + n; }    // lane j <- lane j - n (0 below)
 constexpr int DPP_ROW_ROR(int n) { return 0x120 + n; }    // lane j <- lane (j - n) mod 16
 constexpr int DPP_ROW_BCAST(int n) { return 0x150 + n; }  // every lane <- lane n of its row
@@ -135,7 +146,7 @@ template <class F>
 __device__ __forceinline__ uint64_t lp_carry64(uint64_t v) {
   const uint32_t j = lane16();
   const bool top = j == uint32_t(F::NL - 1);
-  const uint64_t c = top ? 0 : (v >> F::B);
+  const uint64_t c = top ? 0 : uint64_t(int64_t(v) >> F::B);
   const uint64_t m = top ? v : (v & F::MASK);
   return m + dpp64<DPP_ROW_SHR(1)>(c);
 }
@@ -144,9 +155,20 @@ template <class F>
 __device__ __forceinline__ uint32_t lp_carry32(uint32_t v) {
   const uint32_t j = lane16();
   const bool top = j == uint32_t(F::NL - 1);
-  const uint32_t c = top ? 0u : (v >> F::B);
+  const uint32_t c = top ? 0u : uint32_t(int32_t(v) >> F::B);
   const uint32_t m = top ? v : (v & F::MASK);
   return m + dpp32<DPP_ROW_SHR(1)>(c);
+}
+
+// the same where 29-bit limbs leave no room for a doubled operand squared
+template <class F>
+__device__ __forceinline__ uint32_t lp_carry32_if29(uint32_t v) {
+  if constexpr (F::B > 28) return lp_carry32<F>(v);
+  else return v;
+}
+
+__device__ __forceinline__ uint64_t lp_term(uint32_t a, uint32_t b) {
+  return uint64_t(int64_t(int32_t(a)) * int64_t(int32_t(b)));
 }
 
 // Montgomery product a b / R of the four row elements
@@ -159,12 +181,11 @@ __device__ __forceinline__ uint32_t lp_mul(uint32_t a, uint32_t b, const LpK<F>&
     constexpr int i = I;
     const uint32_t ai = dpp32<DPP_ROW_BCAST(i)>(a);
     if constexpr (i == 0) {
-      lo = uint64_t(ai) * b;
+      lo = lp_term(ai, b);
     } else {
-      const uint32_t br = dpp32<DPP_ROW_ROR(i)>(b);
-      const uint32_t ml = j >= uint32_t(i) ? ai : 0u;
-      lo += uint64_t(ml) * br;
-      hi += uint64_t(ai - ml) * br;
+      // b_{j-i} for j >= i, and b_{j-i+16} for j < i (0 past limb NL - 1)
+      lo += lp_term(ai, dpp32<DPP_ROW_SHR(i)>(b));
+      if constexpr (i > 16 - NL) hi += lp_term(ai, dpp32<DPP_ROW_SHL(16 - i)>(b));
     }
   });
   constexpr uint32_t P0 = F::P.w[0];
@@ -174,8 +195,8 @@ __device__ __forceinline__ uint32_t lp_mul(uint32_t a, uint32_t b, const LpK<F>&
     const uint64_t ci = dpp64<DPP_ROW_BCAST(i)>(lo) + carry;
     const uint32_t q = (uint32_t(ci) * F::QINV) & F::MASK;
     lo += uint64_t(q) * k.plo[i];
-    hi += uint64_t(q) * k.phi[i];
-    carry = (ci + uint64_t(q) * P0) >> F::B;
+    if constexpr (i > 16 - NL) hi += uint64_t(q) * k.phi[i];
+    carry = uint64_t(int64_t(ci + uint64_t(q) * P0) >> F::B);
   });
   // lane r <- column NL + r: low columns of lanes NL..15, then high columns
   constexpr int ROT = 16 - NL;
@@ -190,12 +211,17 @@ __device__ __forceinline__ uint32_t lp_mul(uint32_t a, uint32_t b, const LpK<F>&
 
 __device__ __forceinline__ uint32_t lp_add(uint32_t a, uint32_t b) { return a + b; }
 
-// value < 16p with limbs below the top one < 2^(B+3) -> value < 2p, limbs <= 2^B
+// 0 <= value < 16p with limbs below the top one in [0, 2^(B+3)) -> value < 2p,
+// limbs <= 2^B
 template <class F>
 __device__ __forceinline__ uint32_t lp_reduce(uint32_t v, const LpK<F>& k) {
   constexpr uint32_t PTOP = F::P.w[F::NL - 1];
   constexpr uint32_t QR = uint32_t((uint64_t(1) << 32) / (uint64_t(PTOP) + 1));
-  v = lp_carry32<F>(v);
+  {
+    const bool top = lane16() == uint32_t(F::NL - 1);
+    const uint32_t c = top ? 0u : (v >> F::B);
+    v = (top ? v : (v & F::MASK)) + dpp32<DPP_ROW_SHR(1)>(c);
+  }
   // q <= top / (PTOP + 1) <= floor(v / p), and v - q p < 2p
   const uint32_t t = dpp32<DPP_ROW_BCAST(F::NL - 1)>(v);
   const uint32_t q = __umulhi(t, QR);
@@ -212,42 +238,16 @@ __device__ __forceinline__ uint32_t lp_reduce(uint32_t v, const LpK<F>& k) {
   return uint32_t(d);
 }
 
-// a - b (a < 8p with limbs below the top one < 4 2^B, b < 6p with limbs
-// below the top one < 3 2^B - 3: a + 8p - b then has non-negative limbs below
-// 2^(B+3), the top one included, and a value below 16p, the domain of
-// lp_reduce)
+// a signed value back below 2p: adds 8p in the redundant form whose limbs
+// exceed any negative one
 template <class F>
-__device__ __forceinline__ uint32_t lp_sub(uint32_t a, uint32_t b, const LpK<F>& k) {
-  return lp_reduce<F>(a + k.bias - b, k);
+__device__ __forceinline__ uint32_t lp_fix(uint32_t v, const LpK<F>& k) {
+  return lp_reduce<F>(v + k.bias, k);
 }
 
-// bit length of p, and whether R / p >= 2^10: then the largest product an
-// unreduced Y enters, (2Y)^2 < 400 p^2, still has (a b + M q) / R < 2p
 template <class F>
-constexpr int lp_p_bits() {
-  uint32_t t = F::P.w[F::NL - 1];
-  int b = 0;
-  while (t) {
-    b++;
-    t >>= 1;
-  }
-  return F::B * (F::NL - 1) + b;
-}
-template <class F>
-constexpr bool lp_lazy_y() {
-  return F::B * F::NL - lp_p_bits<F>() >= 10;
-}
-
-// a - b for a Y coordinate (a, b product outputs): where lp_lazy_y holds,
-// a + 8p - b after one carry pass (value below 10p, limbs below 2^B + 16),
-// without the quotient and the signed carries of lp_sub
-template <class F>
-__device__ __forceinline__ uint32_t lp_sub_y(uint32_t a, uint32_t b, const LpK<F>& k) {
-  if constexpr (lp_lazy_y<F>()) {
-    return lp_carry32<F>(a + k.bias - b);
-  } else {
-    return lp_sub<F>(a, b, k);
-  }
+__device__ __forceinline__ uint32_t lp_sub(uint32_t a, uint32_t b) {
+  return lp_carry32<F>(a - b);
 }
 
 // canonical form (limbs < 2^B, value < p) of a value < 2p with limbs < 2^31
@@ -276,10 +276,15 @@ __device__ __forceinline__ uint32_t lp_canonical(uint32_t v, const LpK<F>& k) {
   return v;
 }
 
-// the value is 0 mod p (all four rows hold the same element: wave-uniform)
+// the value (|v| < 4p, its lowest limb in [0, 2^B)) is 0 mod p; all four rows hold
+// the same element: wave-uniform.  The multiples of p in the range differ in
+// their low B bits, which settle all but about one other value in 2^24.
 template <class F>
 __device__ __forceinline__ bool lp_is_zero(uint32_t v, const LpK<F>& k) {
-  return __ballot(lp_canonical<F>(v, k) != 0) == 0;
+  constexpr uint32_t pinv = (0u - F::QINV) & F::MASK;
+  const uint32_t t = uint32_t(__builtin_amdgcn_readfirstlane(int(v))) * pinv;
+  if (((t + 4u) & F::MASK) > 8u) return false;
+  return __ballot(lp_canonical<F>(lp_fix<F>(v, k), k) != 0) == 0;
 }
 
 // element r of a wave whose rows hold a0..a3
@@ -330,22 +335,18 @@ __device__ __forceinline__ LpPoint<C> lp_dbl(const LpPoint<C>& P, const LpK<type
   using F = typename C::F;
   static_assert(!C::A_IS_MINUS3, "the lane-parallel doubling is written for a = 0");
   if (P.inf) return P;
-  const uint32_t U = lp_add(P.Y, P.Y);
+  const uint32_t U = lp_carry32_if29<F>(lp_add(P.Y, P.Y));
   uint32_t z = lp_mul<F>(lp_rows(U, P.X, U, P.X), lp_rows(U, P.X, U, P.X), k);
   const uint32_t V = lp_take(z, 0), XX = lp_take(z, 1);
   const uint32_t M = lp_carry32<F>(XX + XX + XX);
   z = lp_mul<F>(lp_rows(U, P.X, V, M), lp_rows(V, V, P.ZZ, M), k);
   const uint32_t W = lp_take(z, 0), S = lp_take(z, 1), ZZ3 = lp_take(z, 2), MM = lp_take(z, 3);
-  // X3 = M^2 - 2S (row 0) and S - X3 = 3S - M^2 (the other rows) in one
-  // reduction: 3S < 6p has limbs below 3 (2^B + 2^9) < 4 2^B
-  const bool r0 = row4() == 0u;
-  const uint32_t S2 = S + S;
-  const uint32_t d = lp_sub<F>(r0 ? MM : S2 + S, r0 ? S2 : MM, k);
-  const uint32_t X3 = lp_take(d, 0), T = lp_take(d, 1);
+  const uint32_t X3 = lp_sub<F>(MM, S + S);
+  const uint32_t T = S - X3;
   z = lp_mul<F>(lp_rows(M, W, W, W), lp_rows(T, P.Y, P.ZZZ, P.ZZZ), k);
   LpPoint<C> R;
   R.X = X3;
-  R.Y = lp_sub_y<F>(lp_take(z, 0), lp_take(z, 1), k);
+  R.Y = lp_sub<F>(lp_take(z, 0), lp_take(z, 1));
   R.ZZ = ZZ3;
   R.ZZZ = lp_take(z, 2);
   R.inf = false;
@@ -362,12 +363,12 @@ __device__ __forceinline__ LpPoint<C> lp_add_pts(const LpPoint<C>& A, const LpPo
   if (A.inf) return B;
   if (B.inf) return A;
   uint32_t z = lp_mul<F>(lp_rows(A.X, B.X, A.Y, B.Y), lp_rows(B.ZZ, A.ZZ, B.ZZZ, A.ZZZ), k);
-  // rows (U1, U2, S1, S2) -> (U1 U1 S1 S1) and (U2 U2 S2 S2): one reduction
+  // rows (U1, U2, S1, S2) -> (U1 U1 S1 S1) and (U2 U2 S2 S2): one difference
   // gives P = U2 - U1 in rows 0-1 and R = S2 - S1 in rows 2-3
   const auto e = __builtin_amdgcn_permlane16_swap(z, z, false, false);
   const auto us1 = __builtin_amdgcn_permlane32_swap(e[0], e[0], false, false);
   const uint32_t U1 = us1[0], S1 = us1[1];
-  const uint32_t d = lp_sub<F>(e[1], e[0], k);
+  const uint32_t d = lp_sub<F>(e[1], e[0]);
   const auto pr = __builtin_amdgcn_permlane32_swap(d, d, false, false);
   const uint32_t P = pr[0], R = pr[1];
   if (lp_is_zero<F>(P, k)) {
@@ -380,18 +381,12 @@ __device__ __forceinline__ LpPoint<C> lp_add_pts(const LpPoint<C>& A, const LpPo
   const uint32_t PP = lp_take(z, 0), RR = lp_take(z, 1), Zf = lp_take(z, 2), Zzf = lp_take(z, 3);
   z = lp_mul<F>(lp_rows(P, U1, Zf, Zf), PP, k);
   const uint32_t PPP = lp_take(z, 0), Q = lp_take(z, 1), ZZ3 = lp_take(z, 2);
-  // X3 = R^2 - (PPP + 2Q) (row 0) and Q - X3 = (3Q + PPP) - R^2 (the other
-  // rows) in one reduction; one carry pass first brings the limbs of the
-  // sums (values below 6p and 8p) under 2^B + 16
-  const bool r0 = row4() == 0u;
-  const uint32_t Q2 = Q + Q;
-  const uint32_t c = lp_carry32<F>(r0 ? PPP + Q2 : Q2 + Q + PPP);
-  const uint32_t x = lp_sub<F>(r0 ? RR : c, r0 ? c : RR, k);
-  const uint32_t X3 = lp_take(x, 0), T = lp_take(x, 1);
+  const uint32_t X3 = lp_sub<F>(RR - PPP, Q + Q);
+  const uint32_t T = Q - X3;
   z = lp_mul<F>(lp_rows(R, S1, Zzf, Zzf), lp_rows(T, PPP, PPP, PPP), k);
   LpPoint<C> O;
   O.X = X3;
-  O.Y = lp_sub_y<F>(lp_take(z, 0), lp_take(z, 1), k);
+  O.Y = lp_sub<F>(lp_take(z, 0), lp_take(z, 1));
   O.ZZ = ZZ3;
   O.ZZZ = lp_take(z, 2);
   O.inf = false;
@@ -417,8 +412,8 @@ __device__ __forceinline__ void lp_point_store(uint32_t* p, const LpPoint<C>& P,
   using F = typename C::F;
   constexpr int CW = F::CW;
   constexpr Words<F::NL> ONE = F::ONE;
-  uint32_t X = lp_canonical<F>(P.X, k), Y = lp_canonical<F>(lp_reduce<F>(P.Y, k), k);
-  uint32_t ZZ = lp_canonical<F>(P.ZZ, k), ZZZ = lp_canonical<F>(P.ZZZ, k);
+  auto canon = [&](uint32_t v) { return lp_canonical<F>(lp_fix<F>(v, k), k); };
+  uint32_t X = canon(P.X), Y = canon(P.Y), ZZ = canon(P.ZZ), ZZZ = canon(P.ZZZ);
   if (P.inf) {
     X = Y = lp_const<F>(ONE);
     ZZ = ZZZ = 0;
@@ -438,10 +433,11 @@ __device__ __forceinline__ XYZZ<C> lp_point_to_xyzz(const LpPoint<C>& P, const L
   using F = typename C::F;
   if (P.inf) return xyzz_inf<C>();
   XYZZ<C> R;
-  R.X = lp_to_fp<F>(lp_canonical<F>(P.X, k));
-  R.Y = lp_to_fp<F>(lp_canonical<F>(lp_reduce<F>(P.Y, k), k));
-  R.ZZ = lp_to_fp<F>(lp_canonical<F>(P.ZZ, k));
-  R.ZZZ = lp_to_fp<F>(lp_canonical<F>(P.ZZZ, k));
+  auto canon = [&](uint32_t v) { return lp_to_fp<F>(lp_canonical<F>(lp_fix<F>(v, k), k)); };
+  R.X = canon(P.X);
+  R.Y = canon(P.Y);
+  R.ZZ = canon(P.ZZ);
+  R.ZZZ = canon(P.ZZZ);
   return R;
 }
 
