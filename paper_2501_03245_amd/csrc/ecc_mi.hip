@@ -696,7 +696,7 @@ ecc_status enqueue_msm(ecc_ctx* ctx, const Geometry& g, const uint32_t* d_bases_
     ECC_TRY(scan_u32(ctx, P<uint32_t>(ctx->counts), P<uint32_t>(ctx->offsets), g.B + 1,
                      P<uint32_t>(ctx->scan_tmp), scan_tmp_words(g.B + 1), st));
     if (g.n) {
-      k_window_group_lds<true><<<m, GROUP_LDS_WG, 0, st>>>(g_scal, P<uint8_t>(ctx->skip), d_msms, g_bits, nullptr,
+      k_window_group_lds<true><<<dim3(m, GROUP_LDS_SPLIT), GROUP_LDS_WG, 0, st>>>(g_scal, P<uint8_t>(ctx->skip), d_msms, g_bits, nullptr,
                                                             P<uint32_t>(ctx->offsets), P<uint32_t>(ctx->sorted),
                                                             d_flags);
       HIP_TRY(hipGetLastError());

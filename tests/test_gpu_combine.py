@@ -10,7 +10,7 @@ import pytest
 import synthetic as syn
 from oracle import c_oracle as co
 from oracle import curves, ref
-from tests.common import points_to_rows, rows_to_points
+from tests.common import points_to_rows, rows_to_points, seeded_bases, seeded_scalars
 
 pytestmark = pytest.mark.gpu
 
@@ -72,3 +72,31 @@ def test_combination_special_cases(name, wc, endo):
         batch = rows_to_points(c, outs.cpu().numpy().view(np.uint64).reshape(m, -1), infs.cpu().numpy())
     assert points_to_rows(c, got).tolist() == points_to_rows(c, want).tolist()
     assert points_to_rows(c, batch).tolist() == points_to_rows(c, want).tolist()
+
+
+@pytest.mark.parametrize("endo", [True, False])
+@pytest.mark.parametrize("wc", [0, 2, 13])
+def test_batch_grouping_split_edges(endo, wc):
+    """MSMs whose windows are grouped by one workgroup and those that share
+    them (more than 2048 grouped points, a point counting twice with the
+    endomorphism split), with fewer windows than workgroups' shares are even
+    (W = 10 or 20 at c = 13) and with points at infinity."""
+    c = curves.BLS12_381
+    at = 1024 if endo else 2048
+    sizes = [at, at + 1, 0, 1, at - 1, 3 * at + 5]
+    offs = np.cumsum([0] + sizes).astype(np.uint64)
+    n = int(offs[-1])
+    _, bases = seeded_bases(c.name, n, 931)
+    bases = bases.copy()
+    bases[::97] = 0
+    s = seeded_scalars(c.name, n, 932, kind="bits")
+    out, inf = co.msm_batch(c.cid, c.limbs, bases, s, offs)
+    m = len(sizes)
+    outs = torch.full((m * 2 * c.limbs,), -1, dtype=torch.int64, device="cuda")
+    infs = torch.full((m,), 255, dtype=torch.uint8, device="cuda")
+    with eccmi.Context(0) as ctx:
+        eccmi.ecc_msm_batch(ctx, c.cid, dev(bases), dev(s), offs, outs, infs,
+                            flags=0 if endo else eccmi.ECC_NO_ENDOMORPHISM, window_c=wc)
+        torch.cuda.synchronize()
+    got = rows_to_points(c, outs.cpu().numpy().view(np.uint64).reshape(m, -1), infs.cpu().numpy())
+    assert got == rows_to_points(c, out, inf)
