@@ -130,8 +130,20 @@ int default_window(ecc_ctx* ctx, int curve, int bits, size_t n_in, size_t n_eff,
   return single ? single_window(n_eff) : batch_window(bits, n_eff);
 }
 
+// Whether a call of m MSMs with E bucket entries sums its buckets directly
+// (accumulate.h).  A design variant runs the batch-affine rounds instead, and so
+// does one BLS12-381 MSM of so many entries (2^24 points at c = 16) that the
+// rounds' latencies and scans are spread thin and their 6 products against 10
+// decide: direct sums against rounds 12.6 and 14.4 ms at 2^22 points, 58.1 and
+// 54.9 at 2^24.  On BN254, whose products cost a third, direct sums win there
+// too: 22.2 and 35.0 ms.
+bool direct_sums(const ecc_ctx* ctx, int curve, size_t m, size_t E) {
+  return ctx->round_variant == 0 && !(curve == ECC_BLS12_381_G1 && m == 1 && E >= (size_t(1) << 28));
+}
+
 // Launch geometry of a batch of MSMs (a single MSM is a batch of one).
 struct Geometry {
+  bool direct = true;         // bucket sums by accumulate.h, else by the batch-affine rounds
   std::vector<MsmDesc> msms;
   std::vector<RedJob> jobs;
   std::vector<RedWave> waves;
@@ -260,6 +272,7 @@ ecc_status build_geometry(ecc_ctx* ctx, int curve, int bits, const uint64_t* siz
     }
   }
   if (open) g.waves.push_back(cur);
+  g.direct = direct_sums(ctx, curve, m, g.E);
   // rounds: a bucket never holds more entries than its MSM has points
   g.rounds = std::min(MAX_ROUNDS, bit_length(g.max_n));
   {
@@ -411,10 +424,6 @@ bool finish_enabled(const ecc_ctx* ctx, size_t m) {
   return (ctx->round_variant & RV_FINISH) || (m == 1 && !(ctx->round_variant & RV_ROUNDS_ONLY));
 }
 
-// Whether a call sums its buckets directly (accumulate.h); a design variant of
-// the rounds runs the batch-affine rounds instead.
-bool direct_sums(const ecc_ctx* ctx) { return ctx->round_variant == 0; }
-
 // entries per work item of the direct sums, from the bound on all entries
 uint32_t acc_cap(const ecc_ctx* ctx, size_t E) {
   const size_t lanes = size_t(ctx->cu_count) * 4 * 64 * 2;  // two waves on each SIMD
@@ -439,7 +448,7 @@ ecc_status reserve_msm(ecc_ctx* ctx, const Geometry& g, uint32_t lanes_max) {
   ECC_TRY(ensure(ctx, ctx->offsets, (g.B + 1) * 4));
   ECC_TRY(ensure(ctx, ctx->cursor, g.B * 4));
   ECC_TRY(ensure(ctx, ctx->sorted, g.E * 4));
-  if (direct_sums(ctx)) {
+  if (g.direct) {
     const size_t extra = acc_extra(ctx, g.E);
     ECC_TRY(ensure(ctx, ctx->psum, (g.B + extra) * XW * 4));
     ECC_TRY(ensure(ctx, ctx->aitems, (std::min(g.B, g.E) + extra) * sizeof(AccItem)));
@@ -709,7 +718,7 @@ ecc_status enqueue_msm(ecc_ctx* ctx, const Geometry& g, const uint32_t* d_bases_
   int nr = 0;
   uint64_t adds = 0;
   bool finish = false;
-  if (direct_sums(ctx)) {
+  if (g.direct) {
     ECC_TRY(enqueue_direct<C>(ctx, g, st, prof, &nr, &finish));
   } else {
     ECC_TRY(enqueue_rounds<C>(ctx, g, st, lanes_max, exact_rounds, &nr, &adds, &finish));
@@ -910,7 +919,7 @@ ecc_status msm_batch_impl(ecc_ctx* ctx, const uint64_t* bases_in, const uint64_t
   }
   HIP_TRY(hipStreamSynchronize(st));
   if (ctx->profiling && !use_graph) {
-    if (direct_sums(ctx) && g.B) {
+    if (g.direct && g.B) {
       // additions of the accumulation: entries less work items
       HIP_TRY(hipMemcpyAsync(ctx->host_small, P<uint32_t>(ctx->ameta), 4, hipMemcpyDeviceToHost, st));
       HIP_TRY(hipMemcpyAsync(ctx->host_small + 1, P<uint32_t>(ctx->offsets) + g.B, 4, hipMemcpyDeviceToHost, st));
