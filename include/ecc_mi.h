@@ -249,7 +249,7 @@ ecc_status ecc_verify_batch(ecc_ctx *ctx, ecc_curve curve, const uint8_t *hashes
  * and valid are DEVICE pointers with the layouts of ecc_verify_batch, owned
  * by the caller.  The device memory the work needs (the generator's comb
  * tables and one table of d Q per request) is a fixed array inside the
- * library, about 15 MB on every GPU the call runs on, held until the process
+ * library, about 17 MB on every GPU the call runs on, held until the process
  * ends; the first call on a device builds the comb tables there.  Every call
  * on one GPU uses that same array: calls that overlap on one GPU (from
  * several threads or streams) race, so the caller orders them.  At most

@@ -9,6 +9,8 @@
 //   counts   : one u32 per bucket (window w, |digit| d) = w * D + d - 1
 //   offsets  : exclusive prefix sums of counts (B + 1 entries)
 //   sorted   : E entries, point index | sign << 31, grouped by bucket
+// and, where a design variant runs the batch-affine rounds (accumulate.h holds
+// the default bucket sums and their buffers):
 //   slots A/B: two buffers of E + B + 2 entries, each an x plane and a y
 //              plane of CW words per entry; round r writes A (r even) or B
 //              (r odd); bucket b's entries start at bucket_slot(offsets[b], b)

@@ -100,3 +100,31 @@ def test_batch_grouping_split_edges(endo, wc):
         torch.cuda.synchronize()
     got = rows_to_points(c, outs.cpu().numpy().view(np.uint64).reshape(m, -1), infs.cpu().numpy())
     assert got == rows_to_points(c, out, inf)
+
+
+@pytest.mark.parametrize("name", ["bn254", "bls12_381"])
+@pytest.mark.parametrize("endo", [True, False])
+@pytest.mark.parametrize("wc", [12, 13, 14, 15, 16, 17])
+def test_reduction_lanes(name, wc, endo):
+    """Buckets per reduction chain and lanes per addition across the widths at
+    which the host's choice of them changes, alone and as part of a batch."""
+    c = curves.CURVES[name]
+    n = 300
+    _, bases = seeded_bases(name, n, 941)
+    s = seeded_scalars(name, n, 942, kind="bits")
+    s[0] = syn.ints_to_limbs([(1 << c.scalar_bits) - 1], 4)[0]
+    flags = 0 if endo else eccmi.ECC_NO_ENDOMORPHISM
+    bd, sd = dev(bases), dev(s)
+    out, inf = torch.zeros(2 * c.limbs, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.uint8, device="cuda")
+    offs = np.array([0, 100, 101, n], dtype=np.uint64)
+    outs, infs = torch.zeros(6 * c.limbs, dtype=torch.int64, device="cuda"), torch.zeros(3, dtype=torch.uint8, device="cuda")
+    with eccmi.Context(0) as ctx:
+        eccmi.ecc_msm(ctx, c.cid, bd, sd, n, out, inf, flags=flags, window_c=wc)
+        eccmi.ecc_msm_batch(ctx, c.cid, bd, sd, offs, outs, infs, flags=flags, window_c=wc)
+        torch.cuda.synchronize()
+    want, winf = co.msm_batch(c.cid, c.limbs, bases, s, np.array([0, n], dtype=np.uint64))
+    bwant, bwinf = co.msm_batch(c.cid, c.limbs, bases, s, offs)
+    assert rows_to_points(c, out.cpu().numpy().view(np.uint64).reshape(1, -1), inf.cpu().numpy()) == \
+        rows_to_points(c, want, winf)
+    assert rows_to_points(c, outs.cpu().numpy().view(np.uint64).reshape(3, -1), infs.cpu().numpy()) == \
+        rows_to_points(c, bwant, bwinf)
