@@ -13,7 +13,10 @@
 //
 // Infinity is a flag, the same in all four lanes; branches on it and on the
 // exceptional cases are uniform in the quad.  Values and limbs are bounded as
-// in lazy.h.
+// in lazy.h, but for Y3: the difference of two products that are reduced on
+// their own, it lies in (-1.1, 1.1) p with limbs within 2^B, and may be below
+// -p.  The formulas take that, as factor and as subtrahend; what needs (-p, 2p)
+// (lz_semi) multiplies it by one first.
 #pragma once
 #include "lazy.h"
 
