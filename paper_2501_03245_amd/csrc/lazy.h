@@ -24,8 +24,8 @@
 //   lz_carry(a)       : one parallel carry pass: limbs in [-k, 2^B + k) for
 //                       limbs below k 2^B, the same value.
 // The formulas state the values they keep: X in (-3.5, 1.2) p, Y, Z, ZZ, ZZZ
-// product outputs in (-0.2, 1.2) p, but for the Y of a quad's sum (quad.h), the
-// difference of two, in (-1.1, 1.1) p.
+// product outputs in (-0.2, 1.2) p, but for the Y of a sum that a quad has not
+// stored yet (quad.h), the difference of two, in (-1.1, 1.1) p.
 #pragma once
 #include "point.h"
 
@@ -550,7 +550,7 @@ __device__ __forceinline__ XYZZ<C> xz_to_xyzz(const Xz<C>& A, bool inf) {
   if (inf) return xyzz_inf<C>();
   XYZZ<C> r;
   r.X = lz_semi<F>(lz_mul<F>(A.X, lz_one<F>()));  // back into (-p, 2p)
-  r.Y = lz_semi<F>(lz_mul<F>(A.Y, lz_one<F>()));  // a quad's Y reaches below -p
+  r.Y = lz_semi<F>(A.Y);
   r.ZZ = lz_semi<F>(A.ZZ);
   r.ZZZ = lz_semi<F>(A.ZZZ);
   return r;

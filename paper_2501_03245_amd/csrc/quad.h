@@ -15,8 +15,9 @@
 // exceptional cases are uniform in the quad.  Values and limbs are bounded as
 // in lazy.h, but for Y3: the difference of two products that are reduced on
 // their own, it lies in (-1.1, 1.1) p with limbs within 2^B, and may be below
-// -p.  The formulas take that, as factor and as subtrahend; what needs (-p, 2p)
-// (lz_semi) multiplies it by one first.
+// -p.  The formulas take that, as factor and as subtrahend; a stored sum's Y is
+// back in (-0.2, 1.2) p (qz_store: one masked addition there; a product in the
+// reduction instead took 308 -> 335 us of k_reduce_a_xz, by its registers).
 #pragma once
 #include "lazy.h"
 
@@ -218,9 +219,17 @@ __device__ __forceinline__ void qz_load(const uint32_t* __restrict__ p, Qz<C>& A
 template <class C>
 __device__ __forceinline__ void qz_store(uint32_t* __restrict__ p, const Qz<C>& A, bool inf) {
   using F = typename C::F;
-  Lz<F> a = A;
-  if (inf && quad_lane() == 0) a.w[0] = -1;
-  lz_store<F>(p + quad_lane() * F::CW, a);
+  constexpr Words<F::NL> P = F::P;
+  const int q = quad_lane();
+  // Y + p where Y is negative (its top limb decides but for values within
+  // p / 2^16 of 0, which may go either way)
+  const int32_t neg = q == 1 ? A.w[F::NL - 1] >> 31 : 0;
+  Lz<F> a;
+#pragma unroll
+  for (int i = 0; i < F::NL; i++) a.w[i] = A.w[i] + (int32_t(P.w[i]) & neg);
+  a = lz_carry_if29<F>(a);
+  if (inf && q == 0) a.w[0] = -1;
+  lz_store<F>(p + q * F::CW, a);
 }
 
 }  // namespace eccmi
