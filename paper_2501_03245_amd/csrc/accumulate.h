@@ -21,17 +21,20 @@
 // Work items.  A bucket of n entries is cut into P = ceil(n / cap) nearly
 // equal parts, one lane each.  cap is 1.5 times the entries that each lane
 // of a full device (two waves on each SIMD) would get, and at least
-// ACC_MIN_CAP: large calls cut only the buckets that would outlast the rest
-// (a skewed window's), small ones cut every bucket, since a lane's additions
-// form a chain.  Items are ordered by length, longest first, by a counting
+// ACC_MIN_CAP: large calls cut only the buckets that would outlast the rest,
+// small ones cut every bucket, since a lane's additions form a chain.  The
+// entries are the call's own, read on the device: zero digits have none, and
+// with scalars of few bits (a witness of small values) they are a fraction of
+// what the sizes allow.  With cap from that bound, 2^20 BLS12-381 points with
+// 8-bit scalars took 3.06 ms a call, 1.78 ms of it in chains of 192 additions on
+// 5,600 lanes; now 1.55 ms (all scalars 1: 5.14 -> 3.42 ms, 64 bits: 4.02 -> 2.80).
+// Items are ordered by length, longest first, by a counting
 // sort, so that the lanes of a wave end together (buckets of uniform scalars
 // hold 64 +- 8 entries at 2^20 points, and the longest of 64 lanes is 83) and
 // the last waves are short ones.  The partial sums of a cut bucket are added
-// by 1 to 4 lanes, as many as the device has for such buckets; 16 lanes where
-// there are more than four (the few buckets of a skewed top window hold 16 times
-// the entries of the others at 2^16 points, and on one lane each their 17
-// additions outlasted all else: 235 -> 96 us); a workgroup when there
-// are very many.  acuts holds buckets of few parts from its start, of very many
+// by 1 to 4 lanes, as many as the device has for such buckets; by 16 lanes where
+// there are more than four; by workgroups of quads when there are very many.
+// acuts holds buckets of few parts from its start, of very many
 // from the end of its first half, and the others in its second half.
 #pragma once
 #include "kernels.h"
@@ -46,7 +49,12 @@ constexpr int ACC_MERGE_LG_LANES = 4;     // at most 16 lanes add the parts of a
 constexpr uint32_t ACC_MERGE_TARGET = 65536;  // lanes the merge spreads over (one wave per SIMD)
 constexpr uint32_t ACC_QUAD_CUTS = 4096;      // bound on the cut buckets up to which a quad takes the place of a lane
 constexpr uint32_t ACC_MERGE_FEW = 4;     // parts up to which the lanes follow the number of such buckets
-constexpr uint32_t ACC_MERGE_MAX = 256;   // parts beyond which a workgroup adds them
+constexpr uint32_t ACC_MERGE_MAX = 128;   // parts beyond which workgroups of quads add them
+constexpr uint32_t ACC_BIG_CHUNK = 256;   // parts of a very long bucket per workgroup, at least
+constexpr uint32_t ACC_BIG_CHUNKS = 64;   // workgroups a very long bucket is spread over, at most
+constexpr uint32_t ACC_ITEMS_LANE = 4;      // parts of a bucket whose items one lane writes, at most
+constexpr uint32_t ACC_ITEMS_GROUP = 1024;  // and a group of lanes
+constexpr uint32_t ACC_ITEMS_LANES = 16;    // of this many
 constexpr int ACC_PLAN_WG = 1024;
 constexpr int ACC_WG = 256;
 constexpr int ACC_MERGE_WG = 256;
@@ -54,10 +62,11 @@ constexpr int ACC_MERGE_WG = 256;
 // counters of one call, zeroed before it
 struct AccMeta {
   uint32_t items;       // work items
-  uint32_t extra;       // parts beyond the first of their bucket
+  uint32_t extra;       // parts beyond the first of their bucket (k_acc_items counts this and the next three together)
   uint32_t cut;         // cut buckets of at most ACC_MERGE_FEW parts
   uint32_t cut_mid;     // of more, up to ACC_MERGE_MAX
   uint32_t cut_big;     // of more than that
+  uint32_t big_parts;   // the most parts of one bucket among those
   uint32_t hist[ACC_BINS];  // items by bin
   uint32_t cursor[ACC_BINS];
 };
@@ -68,13 +77,21 @@ struct AccItem {
 
 struct AccCut {
   uint32_t bucket, parts, extra;  // part 0 at psum[bucket], part j > 0 at psum[B + extra + j - 1]
+  uint32_t done;                  // chunks of a very long bucket summed so far
 };
 
 struct AccLong {
-  uint32_t at, off, bucket, n, extra;
+  uint32_t at, off, bucket, n, extra, parts;
 };
 
-__host__ __device__ inline uint32_t acc_parts(uint32_t n, uint32_t cap) { return (n + cap - 1) / cap; }
+// cap for a call of this many bucket entries on a device of `lanes` (two waves
+// on each SIMD); entries / cap is at most min(entries / ACC_MIN_CAP, 2 lanes / 3)
+__device__ __forceinline__ uint32_t acc_cap(uint32_t entries, uint32_t lanes) {
+  const uint32_t c = uint32_t((uint64_t(entries) * 3 / 2 + lanes - 1) / lanes);
+  return c < ACC_MIN_CAP ? ACC_MIN_CAP : c;
+}
+
+__device__ __forceinline__ uint32_t acc_parts(uint32_t n, uint32_t cap) { return (n + cap - 1) / cap; }
 
 // bin of a bucket's parts: longest first
 __device__ __forceinline__ uint32_t acc_bin(uint32_t n, uint32_t parts) {
@@ -83,9 +100,11 @@ __device__ __forceinline__ uint32_t acc_bin(uint32_t n, uint32_t parts) {
 }
 
 // items per length
-static __global__ void __launch_bounds__(ACC_PLAN_WG) k_acc_count(const uint32_t* __restrict__ counts, uint32_t B,
-                                                                  uint32_t cap, AccMeta* __restrict__ meta) {
+static __global__ void __launch_bounds__(ACC_PLAN_WG) k_acc_count(const uint32_t* __restrict__ counts,
+                                                                  const uint32_t* __restrict__ offsets, uint32_t B,
+                                                                  uint32_t lanes, AccMeta* __restrict__ meta) {
   __shared__ uint32_t s_hist[ACC_BINS];
+  const uint32_t cap = acc_cap(offsets[B], lanes);
   for (uint32_t i = threadIdx.x; i < ACC_BINS; i += ACC_PLAN_WG) s_hist[i] = 0;
   __syncthreads();
   for (uint32_t b = blockIdx.x * ACC_PLAN_WG + threadIdx.x; b < B; b += gridDim.x * ACC_PLAN_WG) {
@@ -99,17 +118,23 @@ static __global__ void __launch_bounds__(ACC_PLAN_WG) k_acc_count(const uint32_t
     if (s_hist[i]) atomicAdd(&meta->hist[i], s_hist[i]);
 }
 
-// the items in order of length, and the lists of cut buckets
+// The items in order of length, and the lists of cut buckets.  Every counter is
+// taken from in LDS first and once per workgroup on the device (2,240 cut buckets
+// among 131,072 took 31 us of device atomics).  The items of a bucket of more than
+// ACC_ITEMS_LANE parts are written by a group of lanes, side by side, or by the
+// whole workgroup (2,048 buckets of 64 parts: 41 us with a lane for each).
 static __global__ void __launch_bounds__(ACC_PLAN_WG) k_acc_items(const uint32_t* __restrict__ counts,
                                                                   const uint32_t* __restrict__ offsets, uint32_t B,
-                                                                  uint32_t cap, AccMeta* __restrict__ meta,
+                                                                  uint32_t lanes, AccMeta* __restrict__ meta,
                                                                   AccItem* __restrict__ items,
                                                                   AccCut* __restrict__ cuts, uint32_t cut_cap) {
   __shared__ uint32_t s_first[ACC_BINS], s_n[ACC_BINS], s_tmp[ACC_PLAN_WG / 64];
-  __shared__ uint32_t s_nlong;
+  __shared__ uint32_t s_cut[4], s_cut0[4];  // parts beyond the first; cut buckets of few, more and very many parts
+  __shared__ uint32_t s_nlong, s_most;
   __shared__ AccLong s_long[ACC_PLAN_WG];
   static_assert(ACC_BINS == ACC_PLAN_WG, "one bin per thread");
   const uint32_t t = threadIdx.x;
+  const uint32_t cap = acc_cap(offsets[B], lanes);
   uint32_t total;
   const uint32_t before = block_exclusive_scan<ACC_PLAN_WG>(meta->hist[t], s_tmp, total);
   if (blockIdx.x == 0 && t == 0) meta->items = total;
@@ -117,41 +142,57 @@ static __global__ void __launch_bounds__(ACC_PLAN_WG) k_acc_items(const uint32_t
   const uint32_t n = b < B ? counts[b] : 0u;
   const uint32_t parts = acc_parts(n, cap);
   const uint32_t bin = n ? acc_bin(n, parts) : 0u;
+  const int kind = parts <= 1 ? 0 : parts <= ACC_MERGE_FEW ? 1 : parts <= ACC_MERGE_MAX ? 2 : 3;
   s_n[t] = 0;
-  if (t == 0) s_nlong = 0;
+  if (t < 4) s_cut[t] = 0;
+  if (t == 0) s_nlong = s_most = 0;
   __syncthreads();
   const uint32_t mine = n ? atomicAdd(&s_n[bin], parts) : 0u;
+  const uint32_t my_extra = kind ? atomicAdd(&s_cut[0], parts - 1) : 0u;
+  const uint32_t my_cut = kind ? atomicAdd(&s_cut[kind], 1u) : 0u;
+  if (kind == 3) atomicMax(&s_most, parts);
   __syncthreads();
   s_first[t] = before + (s_n[t] ? atomicAdd(&meta->cursor[t], s_n[t]) : 0u);
+  if (t < 4 && s_cut[t]) s_cut0[t] = atomicAdd(&meta->extra + t, s_cut[t]);
+  if (t == 0 && s_most) atomicMax(&meta->big_parts, s_most);
   __syncthreads();
-  auto put = [&](uint32_t at, uint32_t off, uint32_t bucket, uint32_t entries, uint32_t np, uint32_t extra,
+  // part j of np: q entries, one more in each of the last r
+  auto put = [&](uint32_t at, uint32_t off, uint32_t bucket, uint32_t q, uint32_t r, uint32_t np, uint32_t extra,
                  uint32_t j) {
-    const uint32_t lo = uint32_t(uint64_t(entries) * j / np), hi = uint32_t(uint64_t(entries) * (j + 1) / np);
-    items[at + j] = AccItem{off + lo, hi - lo, j == 0 ? bucket : B + extra + j - 1, 0u};
+    const uint32_t longer = j + r > np ? j + r - np : 0u;  // longer parts before this one
+    items[at + j] = AccItem{off + j * q + longer, q + (j + r >= np ? 1u : 0u), j == 0 ? bucket : B + extra + j - 1, 0u};
   };
   if (n != 0) {
     const uint32_t at = s_first[bin] + mine, off = offsets[b];
     uint32_t extra = 0;
-    if (parts > 1) {
-      extra = atomicAdd(&meta->extra, parts - 1);
-      const AccCut cut{b, parts, extra};
-      if (parts <= ACC_MERGE_FEW) cuts[atomicAdd(&meta->cut, 1u)] = cut;
-      else if (parts <= ACC_MERGE_MAX) cuts[cut_cap + atomicAdd(&meta->cut_mid, 1u)] = cut;
-      else cuts[cut_cap - 1 - atomicAdd(&meta->cut_big, 1u)] = cut;
+    if (kind) {
+      extra = s_cut0[0] + my_extra;
+      const uint32_t c = s_cut0[kind] + my_cut;
+      cuts[kind == 1 ? c : kind == 2 ? cut_cap + c : cut_cap - 1 - c] = AccCut{b, parts, extra, 0u};
     }
-    if (parts <= 64) {
-      for (uint32_t j = 0; j < parts; j++) put(at, off, b, n, parts, extra, j);
+    if (parts <= ACC_ITEMS_LANE) {
+      const uint32_t q = n / parts, r = n % parts;
+      for (uint32_t j = 0; j < parts; j++) put(at, off, b, q, r, parts, extra, j);
     } else {
-      s_long[atomicAdd(&s_nlong, 1u)] = AccLong{at, off, b, n, extra};  // one slot per thread at most
+      s_long[atomicAdd(&s_nlong, 1u)] = AccLong{at, off, b, n, extra, parts};  // one slot per thread at most
     }
   }
   __syncthreads();
-  // the items of a bucket of many parts (a skewed window's) by the whole workgroup
   const uint32_t nlong = s_nlong;
-  for (uint32_t q = 0; q < nlong; q++) {
-    const AccLong g = s_long[q];
-    const uint32_t np = acc_parts(g.n, cap);
-    for (uint32_t j = t; j < np; j += ACC_PLAN_WG) put(g.at, g.off, g.bucket, g.n, np, g.extra, j);
+  for (uint32_t i = t / ACC_ITEMS_LANES; i < nlong; i += ACC_PLAN_WG / ACC_ITEMS_LANES) {
+    const AccLong g = s_long[i];
+    if (g.parts > ACC_ITEMS_GROUP) continue;
+    const uint32_t q = g.n / g.parts, r = g.n % g.parts;
+    for (uint32_t j = t % ACC_ITEMS_LANES; j < g.parts; j += ACC_ITEMS_LANES)
+      put(g.at, g.off, g.bucket, q, r, g.parts, g.extra, j);
+  }
+  if (s_most > ACC_ITEMS_GROUP) {
+    for (uint32_t i = 0; i < nlong; i++) {
+      const AccLong g = s_long[i];
+      if (g.parts <= ACC_ITEMS_GROUP) continue;
+      const uint32_t q = g.n / g.parts, r = g.n % g.parts;
+      for (uint32_t j = t; j < g.parts; j += ACC_PLAN_WG) put(g.at, g.off, g.bucket, q, r, g.parts, g.extra, j);
+    }
   }
 }
 
@@ -232,7 +273,7 @@ __device__ __forceinline__ void acc_merge(Xz<C>& A, bool& inf, const AccCut& cut
     } else {
       const int off = 1 << (tree - 1 - int(st - most));
       xz_map<C>(Bp, A, [&](int32_t v) { return __shfl_down(v, off, 64); });
-      binf = __shfl_down(int(inf), off, 64) != 0 || (l & 63u) + uint32_t(off) >= min(G, 64u);
+      binf = __shfl_down(int(inf), off, 64) != 0 || l + uint32_t(off) >= G;
     }
     xz_add<C>(A, inf, Bp, binf);
   }
@@ -263,7 +304,7 @@ __global__ void __launch_bounds__(ACC_MERGE_WG) __attribute__((amdgpu_waves_per_
     // the wave's cut buckets; the loop's bounds are wave-uniform
     for (uint32_t w = pass == 0 ? waves - 1 - wave : wave; (w << (6 - lgG)) < n; w += waves) {
       const uint32_t i = (w << (6 - lgG)) + ((threadIdx.x & 63u) >> lgG);
-      const AccCut cut = i < n ? list[i] : AccCut{0u, 0u, 0u};
+      const AccCut cut = i < n ? list[i] : AccCut{0u, 0u, 0u, 0u};
       int tree = 0;  // levels the widest of the wave's buckets needs
       while (tree < lgG && __ballot((1u << tree) < cut.parts) != 0) tree++;
       Xz<C> A;
@@ -294,7 +335,7 @@ __global__ void __launch_bounds__(ACC_MERGE_WG) k_acc_merge_quad(const AccMeta* 
     const uint32_t l = t & (G - 1);
     for (uint32_t w = pass == 0 ? waves - 1 - wave : wave; (w << (4 - lgG)) < n; w += waves) {
       const uint32_t i = (w << (4 - lgG)) + (t >> lgG);
-      const AccCut cut = i < n ? list[i] : AccCut{0u, 0u, 0u};
+      const AccCut cut = i < n ? list[i] : AccCut{0u, 0u, 0u, 0u};
       int tree = 0;
       while (tree < lgG && __ballot((1u << tree) < cut.parts) != 0) tree++;
       const uint32_t mine = l < cut.parts ? (cut.parts - l + G - 1) / G : 0u;
@@ -325,31 +366,77 @@ __global__ void __launch_bounds__(ACC_MERGE_WG) k_acc_merge_quad(const AccMeta* 
   }
 }
 
+// The parts of very long buckets (small or repeated scalars fill a few buckets
+// with most of the entries): a workgroup's 64 quads add a chunk of at least
+// ACC_BIG_CHUNK parts, a tree through LDS joins them, and the workgroup that ends
+// last at a bucket adds its chunks' sums (no workgroup waits for another).
+// Bound by that chain: at most 3 additions, 6 levels and the last workgroup's 6
+// levels up to 2^14 parts.  2^18 points with 64-bit scalars: one BLS12-381 bucket
+// of 2,731 parts took 267 us on one workgroup of lanes, its 9,362 parts now 113 us.
 template <class C>
-__global__ void __launch_bounds__(ACC_MERGE_WG) __attribute__((amdgpu_waves_per_eu(2, 2))) k_acc_merge_big(
-    const AccMeta* __restrict__ meta, const AccCut* __restrict__ cuts, uint32_t cut_cap, uint32_t B,
-    uint32_t* __restrict__ psum) {
-  constexpr int NW = ACC_MERGE_WG / 64;
-  __shared__ uint32_t s_pt[NW][xyzz_words<C>()];
+__global__ void __launch_bounds__(ACC_MERGE_WG) k_acc_merge_big(const AccMeta* __restrict__ meta, AccCut* cuts,
+                                                                uint32_t cut_cap, uint32_t B, uint32_t* psum) {
+  using F = typename C::F;
+  constexpr int XW = xyzz_words<C>();
+  constexpr uint32_t QUADS = ACC_MERGE_WG / 4;
+  static_assert(ACC_BIG_CHUNKS <= QUADS, "one quad per chunk sum");
+  __shared__ int32_t s_pt[F::NL * ACC_MERGE_WG];
+  __shared__ int32_t s_inf[QUADS];
+  __shared__ uint32_t s_last;
+  const uint32_t quad = threadIdx.x >> 2;
   const uint32_t n = meta->cut_big;
-  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
-    const AccCut cut = cuts[cut_cap - 1 - i];
-    Xz<C> A;
-    bool inf;
-    acc_merge<C>(A, inf, cut, threadIdx.x, ACC_MERGE_WG, B, psum, 6);
-    if ((threadIdx.x & 63u) == 0) xz_store<C>(s_pt[threadIdx.x / 64], A, inf);
-    __syncthreads();
-    if (threadIdx.x == 0) {
+  const uint32_t most = min(ACC_BIG_CHUNKS, (meta->big_parts + ACC_BIG_CHUNK - 1) / ACC_BIG_CHUNK);
+  // every branch below but those on `quad` and on a point's infinity is uniform in the workgroup
+  for (uint32_t u = blockIdx.x; u < n * most; u += gridDim.x) {
+    AccCut* const list = cuts + (cut_cap - 1 - u % n);
+    const AccCut cut = *list;
+    const uint32_t per = max(ACC_BIG_CHUNK, (cut.parts + ACC_BIG_CHUNKS - 1) / ACC_BIG_CHUNKS);
+    const uint32_t chunks = (cut.parts + per - 1) / per;
+    uint32_t base = u / n * per, stride = 1;
+    if (base >= cut.parts) continue;
+    uint32_t count = min(per, cut.parts - base);
+    // the chunk's parts, then (on the last workgroup) the chunks' sums
 #pragma unroll 1
-      for (int w = 1; w < NW; w++) {
-        Xz<C> Bp;
-        bool binf;
-        xz_load<C>(s_pt[w], Bp, binf);
-        xz_add<C>(A, inf, Bp, binf);
+    for (int pass = 0;; pass++) {
+      int levels = 0;
+      while (levels < 6 && (1u << levels) < count) levels++;
+      const uint32_t own = (count + QUADS - 1) / QUADS;
+      Qz<C> A = lz_one<F>();
+      bool inf = true;
+#pragma unroll 1
+      for (uint32_t st = 0; st < own + uint32_t(levels); st++) {
+        Qz<C> Bp = A;
+        bool binf = true;
+        if (st < own) {
+          const uint32_t i = quad + QUADS * st, j = base + stride * i;
+          if (i < count) qz_load<C>(psum + size_t(j == 0 ? cut.bucket : B + cut.extra + j - 1) * XW, Bp, binf);
+        } else {
+          const uint32_t from = quad + (1u << (levels - 1 - int(st - own)));
+          __syncthreads();
+#pragma unroll
+          for (int k = 0; k < F::NL; k++) s_pt[k * ACC_MERGE_WG + threadIdx.x] = A.w[k];
+          if (quad_lane() == 0) s_inf[quad] = inf ? 1 : 0;
+          __syncthreads();
+          if (from < QUADS) {
+#pragma unroll
+            for (int k = 0; k < F::NL; k++) Bp.w[k] = s_pt[k * ACC_MERGE_WG + from * 4 + quad_lane()];
+            binf = s_inf[from] != 0;
+          }
+        }
+        qz_add<C>(A, inf, Bp, binf);
       }
-      xz_store<C>(psum + size_t(cut.bucket) * xyzz_words<C>(), A, inf);
+      if (quad == 0) qz_store<C>(psum + size_t(base == 0 ? cut.bucket : B + cut.extra + base - 1) * XW, A, inf);
+      if (pass == 1 || chunks == 1) break;
+      __threadfence();  // the sum before the count, at device scope: chunks run on other XCDs too
+      if (threadIdx.x == 0) s_last = atomicAdd(&list->done, 1u) == chunks - 1 ? 1u : 0u;
+      __syncthreads();
+      if (!s_last) break;
+      __threadfence();
+      base = 0;
+      stride = per;
+      count = chunks;
     }
-    __syncthreads();
+    __syncthreads();  // LDS is used again
   }
 }
 

@@ -424,15 +424,15 @@ bool finish_enabled(const ecc_ctx* ctx, size_t m) {
   return (ctx->round_variant & RV_FINISH) || (m == 1 && !(ctx->round_variant & RV_ROUNDS_ONLY));
 }
 
-// entries per work item of the direct sums, from the bound on all entries
-uint32_t acc_cap(const ecc_ctx* ctx, size_t E) {
-  const size_t lanes = size_t(ctx->cu_count) * 4 * 64 * 2;  // two waves on each SIMD
-  return std::max(ACC_MIN_CAP, uint32_t((E + E / 2 + lanes - 1) / lanes));
-}
+// lanes of a full device in the direct sums: two waves on each SIMD
+uint32_t acc_lanes(const ecc_ctx* ctx) { return uint32_t(ctx->cu_count) * 4 * 64 * 2; }
 
 // bound on the parts of cut buckets beyond their first (a bucket of n entries
-// has at most n / cap of them), and so on the number of cut buckets
-size_t acc_extra(const ecc_ctx* ctx, size_t E) { return E / acc_cap(ctx, E) + 1; }
+// has at most n / cap of them, cap being acc_cap of the entries that the call
+// turns out to have), and so on the number of cut buckets
+size_t acc_extra(const ecc_ctx* ctx, size_t E) {
+  return std::min(E / ACC_MIN_CAP, size_t(acc_lanes(ctx)) * 2 / 3) + 1;
+}
 
 // Scratch for a geometry (all device buffers of the context).
 template <class C>
@@ -487,14 +487,14 @@ ecc_status enqueue_direct(ecc_ctx* ctx, const Geometry& g, hipStream_t st, bool 
   AccMeta* meta = P<AccMeta>(ctx->ameta);
   uint32_t* counts = P<uint32_t>(ctx->counts);
   uint32_t* psum = P<uint32_t>(ctx->psum);
-  const uint32_t cap = acc_cap(ctx, g.E);
+  const uint32_t lanes = acc_lanes(ctx);
   const size_t extra = acc_extra(ctx, g.E);
   if (B) {
     ECC_TRY(fill_u32(ctx, P<uint32_t>(ctx->ameta), sizeof(AccMeta) / 4, 0u, st));
     k_acc_count<<<std::min<uint32_t>(ceil_div(B, ACC_PLAN_WG), uint32_t(ctx->cu_count)), ACC_PLAN_WG, 0, st>>>(
-        counts, B, cap, meta);
+        counts, P<uint32_t>(ctx->offsets), B, lanes, meta);
     HIP_TRY(hipGetLastError());
-    k_acc_items<<<ceil_div(B, ACC_PLAN_WG), ACC_PLAN_WG, 0, st>>>(counts, P<uint32_t>(ctx->offsets), B, cap, meta,
+    k_acc_items<<<ceil_div(B, ACC_PLAN_WG), ACC_PLAN_WG, 0, st>>>(counts, P<uint32_t>(ctx->offsets), B, lanes, meta,
                                                                   P<AccItem>(ctx->aitems), P<AccCut>(ctx->acuts),
                                                                   uint32_t(extra));
     HIP_TRY(hipGetLastError());
@@ -507,7 +507,9 @@ ecc_status enqueue_direct(ecc_ctx* ctx, const Geometry& g, hipStream_t st, bool 
   HIP_TRY(hipGetLastError());
   if (prof) ECC_TRY(record(ctx, 3, st));
   *nr = 1;
-  if (g.max_n > cap) {  // no bucket holds more entries than its MSM has points
+  // no bucket holds more entries than its MSM has points; how many parts that is
+  // is known on the device only, where few entries are cut at ACC_MIN_CAP
+  if (g.max_n > ACC_MIN_CAP) {
     if (prof) ECC_TRY(record(ctx, 4, st));
     const size_t cuts = std::min<size_t>(B, extra);
     if (cuts <= ACC_QUAD_CUTS) {
@@ -518,8 +520,9 @@ ecc_status enqueue_direct(ecc_ctx* ctx, const Geometry& g, hipStream_t st, bool 
       k_acc_merge<C><<<blocks, ACC_MERGE_WG, 0, st>>>(meta, P<AccCut>(ctx->acuts), uint32_t(extra), B, psum);
     }
     HIP_TRY(hipGetLastError());
-    if (g.max_n > uint64_t(cap) * ACC_MERGE_MAX) {
-      k_acc_merge_big<C><<<256, ACC_MERGE_WG, 0, st>>>(meta, P<AccCut>(ctx->acuts), uint32_t(extra), B, psum);
+    if (g.max_n > ACC_MIN_CAP * ACC_MERGE_MAX) {
+      k_acc_merge_big<C><<<2 * ctx->cu_count, ACC_MERGE_WG, 0, st>>>(meta, P<AccCut>(ctx->acuts), uint32_t(extra), B,
+                                                                     psum);
       HIP_TRY(hipGetLastError());
     }
     if (prof) ECC_TRY(record(ctx, 5, st));
