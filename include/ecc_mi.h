@@ -320,20 +320,24 @@ ecc_status ecc_fixed_base_mul(ecc_ctx *ctx, ecc_curve curve, const uint64_t *ks,
  * The window width c of a Pippenger MSM trades W = ceil((bits + 1) / c)
  * passes over the points against 2^(c-1) buckets per window to reduce; the
  * best value depends on n, the curve and the device.  Without tuning the
- * library takes c from a cost model.  ecc_tune measures, for every n = 2^k
- * with log2n_min <= k <= log2n_max, MSMs over seeded synthetic inputs made on
- * the device (bases k_i G, scalars of the curve's bit length) at the model's
- * c and its neighbours, then the target number of additions per lane in a
- * bucket round and the round kernel's occupancy target at the best c, taking
- * the median of `reps` timed calls; the
- * winners are used by later MSM calls of this context whose size falls in
- * the same power-of-two class (a nonzero opts->window_c still wins).
+ * library takes c = 8 or 16 for one MSM, by its size, and a cost model's c for
+ * each MSM of a batch.  ecc_tune measures, for every n = 2^k
+ * with log2n_min <= k <= log2n_max, one MSM over seeded synthetic inputs made on
+ * the device (bases k_i G, scalars of the curve's bit length) at the library's
+ * c, its neighbours and 16; then, where such a call runs bucket rounds (a design
+ * variant is set, or one BLS12-381 MSM of about 2^24 points or more), the target
+ * number of additions per lane in a round and the round kernel's occupancy
+ * target at the best c.  Each time is the median of `reps` calls.  The
+ * winners are used by later calls of this context for one MSM whose size falls in
+ * the same power-of-two class (a nonzero opts->window_c still wins); the MSMs
+ * of a batch keep the cost model's c.
  * Errors: ECC_ERR_ARG (range outside [1, 26], reps outside [1, 101]),
  * ECC_ERR_UNSUPPORTED (secp256r1), and those of ecc_msm. */
 ecc_status ecc_tune(ecc_ctx *ctx, ecc_curve curve, int log2n_min, int log2n_max, int reps);
 
-/* The window width and additions-per-lane target an MSM of n points would
- * use on this context now. */
+/* The window width a call for one MSM of n points would use on this context
+ * now, and the additions-per-lane target of its bucket rounds, where it runs
+ * them. */
 ecc_status ecc_tuned_params(ecc_ctx *ctx, ecc_curve curve, size_t n, int *window_c, int *adds_per_lane);
 
 /* Write the context's tuned entries to a text file (one line per entry:

@@ -123,11 +123,15 @@ int batch_window(int bits, size_t n) {
 
 // n_in: points given by the caller (the tuned table's index); bits and n_eff:
 // scalar bits and points of the bucket work (2 n_in points of half-length
-// scalars after the endomorphism split); single: the call's only MSM
+// scalars after the endomorphism split); single: the call's only MSM.  The tuned
+// table is measured on one MSM alone and says nothing about the MSMs of a batch:
+// 2048 BLS12-381 MSMs of 2^4 points take 1.93 ms at their own width and 3.50 ms at 8,
+// 512 of 2^11 points 6.2 ms and 79 ms at 16, which a tuner may pick for one of them.
 int default_window(ecc_ctx* ctx, int curve, int bits, size_t n_in, size_t n_eff, bool single) {
+  if (!single) return batch_window(bits, n_eff);
   int lg = bit_length(n_in ? n_in : 1) - 1;
   if (lg < 32 && ctx->tuned[curve][lg] > 0) return ctx->tuned[curve][lg];
-  return single ? single_window(n_eff) : batch_window(bits, n_eff);
+  return single_window(n_eff);
 }
 
 // Whether a call of m MSMs with E bucket entries sums its buckets directly
@@ -1078,10 +1082,10 @@ ecc_status tune_impl(ecc_ctx* ctx, int lg_lo, int lg_hi, int reps) {
     int best_c = c0;
     double best = 1e300;
     ctx->kmin_override = KMIN;
-    // the model's neighbourhood, and the widest window the two-level sort
-    // takes (often the fastest: fewer windows, and the sort stays in LDS)
+    // the rule's neighbourhood (5 to 12 or 13 to 18), and the widest window the
+    // two-level sort takes
     std::vector<int> cands;
-    for (int c = std::max(2, c0 - 3); c <= std::min(20, c0 + 2); c++) cands.push_back(c);
+    for (int c = std::max(2, c0 - 3); c <= std::min(20, c0 + (c0 < RADIX_SORT_MAX_C ? 4 : 2)); c++) cands.push_back(c);
     if (std::find(cands.begin(), cands.end(), int(RADIX_SORT_MAX_C)) == cands.end())
       cands.push_back(int(RADIX_SORT_MAX_C));
     for (int c : cands) {
@@ -1093,9 +1097,18 @@ ecc_status tune_impl(ecc_ctx* ctx, int lg_lo, int lg_hi, int reps) {
         best_c = c;
       }
     }
+    // the rounds' parameters, where such an MSM runs them: the direct sums read
+    // neither, and the times of equal calls would pick one by chance
+    bool rounds = false;
+    if (s == ECC_OK) {
+      Geometry g;
+      const uint64_t one = n;
+      s = build_geometry(ctx, C::ID, C::SCALAR_BITS, &one, 1, best_c, g, glv_bits_of<C>());
+      rounds = !g.direct;
+    }
     int best_k = KMIN;
     for (int k : {2, 4, 16}) {
-      if (s != ECC_OK) break;
+      if (s != ECC_OK || !rounds) break;
       ctx->kmin_override = k;
       double ms = 0;
       s = time_msm<C>(ctx, bases, scal, n, out, inf, best_c, reps, &ms);
@@ -1107,7 +1120,7 @@ ecc_status tune_impl(ecc_ctx* ctx, int lg_lo, int lg_hi, int reps) {
     int best_o = ROUND_OCC;
     ctx->kmin_override = best_k;
     for (int o : {2}) {
-      if (s != ECC_OK) break;
+      if (s != ECC_OK || !rounds) break;
       ctx->occ_override = o;
       double ms = 0;
       s = time_msm<C>(ctx, bases, scal, n, out, inf, best_c, reps, &ms);
