@@ -558,6 +558,8 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 // The same with a quad of lanes in the place of a lane: a workgroup of 256 is
 // one level-A wave of the plan, and its 64 quads exchange points through LDS.
+// All jobs of a workgroup have the same L (Geometry::same_chain): its threads meet
+// at barriers once per step.
 // Taken while the quads make at most two waves per SIMD, since a chain of
 // about 2 L + 13 + log2 L point operations bounds the phase there: BLS12-381,
 // 1021 points 220 -> 117 us, 2^16 points 235 -> 178 us (1.2 waves per SIMD);

@@ -152,6 +152,7 @@ struct Geometry {
   std::vector<RedJob> jobs;
   std::vector<RedWave> waves;
   std::vector<uint32_t> big;  // jobs spread over more than one wave
+  bool same_chain = true;     // the jobs of every wave have equally many buckets per lane
   size_t n = 0;               // points given by the caller
   bool glv = false;           // single MSM over 2 n points after the endomorphism split (fused ingest)
   bool glv_batch = false;     // the split for any batch: point i -> points 2i, 2i + 1 (k_ingest_glv_batch)
@@ -268,6 +269,7 @@ ecc_status build_geometry(ecc_ctx* ctx, int curve, int bits, const uint64_t* siz
     }
     uint32_t lgS = uint32_t(lgLam);
     if (open && cur.lgS == lgS && cur.njobs < (64u >> lgS)) {
+      g.same_chain = g.same_chain && g.jobs[cur.job].lgD == g.jobs[j].lgD;
       cur.njobs++;
     } else {
       if (open) g.waves.push_back(cur);
@@ -532,7 +534,9 @@ ecc_status enqueue_direct(ecc_ctx* ctx, const Geometry& g, hipStream_t st, bool 
     if (prof) ECC_TRY(record(ctx, 5, st));
     *finished = true;
   }
-  if (g.waves.size() <= 2 * size_t(ctx->cu_count)) {
+  // the quad form meets at barriers, once per step of its jobs' common chain; only
+  // a batch whose lanes were halved (far more waves than this) mixes lengths
+  if (g.same_chain && g.waves.size() <= 2 * size_t(ctx->cu_count)) {
     k_reduce_a_quad<C><<<unsigned(g.waves.size()), REDUCE_QUAD_WG, 0, st>>>(
         counts, psum, GP<RedJob>(ctx, g.off_jobs), GP<RedWave>(ctx, g.off_waves), P<uint32_t>(ctx->segS),
         P<uint32_t>(ctx->segT), P<uint32_t>(ctx->winsum));
