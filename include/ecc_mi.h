@@ -308,7 +308,7 @@ ecc_status ecc_pmul_batch(ecc_ctx *ctx, ecc_curve curve, const uint64_t *points,
 
 /* k_i G for the curve's standard generator G (fixed-point multiplication,
  * the paper's FPMUL with precomputed multiples of G, Section 2.1): one mixed
- * addition per signed digit of k_i (13 bits; 8 bits in a context with an HBM
+ * addition per signed digit of k_i (13 bits; 9 bits in a context with an HBM
  * budget) from a comb table that the context makes once per curve, then
  * one batched inversion for the affine results.  ks: n x 4 u64 scalars (any
  * 256-bit value); out: n points, canonical affine ((0,0) when k_i G is the

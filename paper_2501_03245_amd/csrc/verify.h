@@ -478,16 +478,17 @@ __device__ __forceinline__ void vt_mul(Jz<C>& A, bool& inf, const uint32_t* __re
 //
 // Two widths.  W = 13: 20 additions, 81,920 points (7.9 MB for the 256-bit
 // primes, which passes through the 4 MB L2s but stays in the 256 MB cache
-// behind them).  W = 8: 33 additions, 4,224 points (0.4 MB), where device
+// behind them).  W = 9: 29 additions, 7,424 points (0.7 MB), where device
 // memory is capped or fixed.  Unsigned bytes, the earlier form, took 32
-// additions of 8,192 points.  An entry is loaded while the addition of the
+// additions of 8,192 points; W = 8 takes 33 of 4,224, and was slower than they
+// were (2^19 BLS12-381 fixed-point products 2.88 -> 3.02 ms; 2.61 with 9).  An entry is loaded while the addition of the
 // window before it runs, since a gather costs about as long as half an
 // addition.
 // Measured against the unsigned bytes: 2^19 SM2 fixed-point products 0.97 ->
 // 0.66 ms, 2^18 SM2 signatures 0.60 -> 0.45 ms, 2^16 SM2 verifications 1.51 ->
 // 1.46 ms (W = 13).
 constexpr int COMB_WIDE = 13;
-constexpr int COMB_NARROW = 8;
+constexpr int COMB_NARROW = 9;
 template <int W>
 constexpr int comb_windows() {
   return (257 + W - 1) / W;
