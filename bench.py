@@ -50,8 +50,10 @@ def algorithmic_mad32_per_point(n: int, bits: int, curve: int) -> float:
     return best * MULS_PER_AFFINE_ADD * MAD32_PER_MUL[curve]
 
 
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bucket_round_traffic_bls12_381_n2p20.json")
-KERNEL_SOURCES = ["constants.h", "curves.h", "field.h", "inverse.h", "point.h", "kernels.h", "lazy.h", "accumulate.h"]
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bucket_sum_traffic_bls12_381_n2p20.json")
+# accumulate.h and every header it includes
+KERNEL_SOURCES = ["constants.h", "curves.h", "field.h", "inverse.h", "point.h", "lanefield.h", "kernels.h", "lazy.h",
+                  "quad.h", "accumulate.h"]
 
 
 def kernel_source_digest() -> str:
@@ -64,18 +66,44 @@ def kernel_source_digest() -> str:
     return h.hexdigest()
 
 
-def measured_traffic():
+def measured_traffic(kernel: str, cid: int, n: int):
     """HBM bytes per accumulation launch from the committed rocprofv3 counter
     summary (FETCH_SIZE and WRITE_SIZE scaled by a plain copy's readings), or
-    None when the kernel sources changed since the counters were taken."""
+    None for another kernel or workload, or when the kernel sources changed
+    since the counters were taken."""
     try:
         with open(TRAFFIC_FILE) as f:
             t = json.load(f)
     except (OSError, ValueError):
         return None
-    if t.get("source_digest") != kernel_source_digest():
+    if t.get("source_digest") != kernel_source_digest() or (t.get("kernel"), t.get("n")) != (kernel, n) or cid != 2:
         return None
     return t.get("bytes_per_launch")
+
+
+def accumulation_roofline(st: dict, steps: int, cid: int, n: int) -> dict:
+    """The roofline entry of the bucket accumulation, from the profiled stats of
+    `steps` calls.  Direct sums are one launch a call and add in XYZZ
+    coordinates; the batch-affine rounds (design variants, and one BLS12-381 MSM
+    of about 2^24 points or more) are several, with cheaper additions."""
+    rounds = st["round_launches"] > st["msm_calls"]
+    kernel, what, muls = (("k_bucket_round", "batch-affine", MULS_PER_AFFINE_ADD) if rounds
+                          else ("k_bucket_acc", "mixed XYZZ", MULS_PER_XYZZ_ADD))
+    per_add = muls * MAD32_PER_MUL[cid]
+    achieved = st["round_adds"] * per_add / (st["round_ms"] * 1e-3) if st["round_ms"] > 0 else 0.0
+    return {
+        "bound": "alu",
+        "kernel": f"{kernel} (bucket accumulation, {what} additions)",
+        "achieved": achieved / 1e12,
+        "peak": PEAK_MAD32 / 1e12,
+        "unit": "TOP/s",
+        "frac": achieved / PEAK_MAD32,
+        "traffic": measured_traffic(kernel, cid, n),
+        "per_unit": f"{per_add} MAD32 per {what} addition",
+        "units_per_launch": st["round_adds"] / max(1, st["round_launches"]),
+        "avg_launch_ms": st["round_ms"] / max(1, st["round_launches"]),
+        "finishing_pass_ms": st["finish_ms"] / steps,
+    }
 
 
 def batched_vs_plain(eccmi, syn, torch, np, ctx, cid: int, m: int, plain_m: int, seed: int) -> dict:
@@ -686,22 +714,8 @@ def main() -> int:
           f"total {st['total_ms'] / args.steps:.3f}", file=sys.stderr, flush=True)
 
     value = n * args.steps / dt
-    per_add = MULS_PER_XYZZ_ADD * MAD32_PER_MUL[cid]
-    achieved = st["round_adds"] * per_add / (st["round_ms"] * 1e-3) if st["round_ms"] > 0 else 0.0
-    roofline = {
-        "bound": "alu",
-        "kernel": "k_bucket_acc (bucket accumulation, mixed XYZZ additions)",
-        "achieved": achieved / 1e12,
-        "peak": PEAK_MAD32 / 1e12,
-        "unit": "TOP/s",
-        "frac": achieved / PEAK_MAD32,
-        "traffic": measured_traffic(),
-        "per_unit": f"{per_add} MAD32 per mixed XYZZ addition",
-        "units_per_launch": st["round_adds"] / max(1, st["round_launches"]),
-        "avg_launch_ms": st["round_ms"] / max(1, st["round_launches"]),
-        "finishing_pass_ms": st["finish_ms"] / args.steps,
-        "msm_frac": value * algorithmic_mad32_per_point(n, bits, cid) / PEAK_MAD32,
-    }
+    roofline = accumulation_roofline(st, args.steps, cid, n)
+    roofline["msm_frac"] = value * algorithmic_mad32_per_point(n, bits, cid) / PEAK_MAD32
 
     batched = served = configs = table5 = None
     if not args.no_extras and not args.no_configs and cid == 2:
