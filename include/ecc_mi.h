@@ -74,7 +74,7 @@ enum {
                                    (BN254 G1 has cofactor 1, so every curve point is in it) */
   ECC_VERIFY_BATCHED = 1u << 5,  /* ecc_verify_batch: the batched-affine form (one GAS
                                     inversion per scalar bit and workgroup, Section 3.4) */
-  ECC_VERIFY_PER_LANE = 1u << 6, /* ecc_verify_batch: the per-lane XYZZ form (two inversions
+  ECC_VERIFY_PER_LANE = 1u << 6, /* ecc_verify_batch: the per-lane form (two inversions
                                     per launch); also the form used when neither flag is set */
   ECC_ASYNC = 1u << 7,           /* ecc_msm, ecc_msm_batch, ecc_verify_batch: enqueue on the
                                     stream and return without waiting (device pointers
@@ -89,7 +89,7 @@ enum {
                                     Algorithm 3): affine addition and doubling per scalar
                                     bit sharing one Montgomery-trick chain per lane, one
                                     GAS inversion per bit and workgroup, several requests
-                                    per lane; the default is the per-lane XYZZ form */
+                                    per lane; the default is the per-lane form */
 };
 
 typedef struct ecc_ctx ecc_ctx;
@@ -222,9 +222,10 @@ ecc_status ecc_msm_batch_scratch_bytes(ecc_ctx *ctx, ecc_curve curve, const uint
  *    Gather-Apply-Scatter inversion per workgroup and scalar bit (Sections
  *    3.2-3.4, Algorithm 3); a launch takes 257 inversion latencies however
  *    few requests it holds;
- *  - per lane (ECC_VERIFY_PER_LANE): each request's double-scalar sum in XYZZ
- *    coordinates on its own lane (4-bit windows of u2 over a per-request table
- *    of d Q, a comb table of G for u1), with two batched inversions
+ *  - per lane (ECC_VERIFY_PER_LANE): each request's double-scalar sum on its
+ *    own lane, or on four lanes in calls of at most 2^14 requests: signed 4-bit
+ *    windows of u2 over a per-request table of d Q (d = 1..8), then signed digits
+ *    of u1 from a comb table of G, with two batched inversions
  *    per launch.  This is the default: it measured faster at every batch
  *    size, in latency and in throughput.
  * The inverses of s mod n are batched per workgroup in both.
@@ -267,7 +268,8 @@ size_t ecc_verify_batch_noalloc_max(void);
  * Request i: with 1 <= d_i, k_i <= n - 1, R = k_i G, r = R.x mod n,
  * e = the hash read as a big-endian integer, s = k_i^-1 (e + r d_i) mod n.
  * k_i G is summed from a comb table of G (made once per context)
- * in XYZZ coordinates, one request per lane; R.x's denominator and k_i are
+ * in XYZZ coordinates, one request per lane (per four lanes in calls of at
+ * most 2^14 requests); R.x's denominator and k_i are
  * inverted by one Gather-Apply-Scatter batch inversion each per workgroup.
  *   hashes   : m x 32 bytes (big-endian digests)
  *   privkeys : m x 4 u64 little-endian private keys d_i
@@ -283,10 +285,12 @@ ecc_status ecc_sign_batch(ecc_ctx *ctx, ecc_curve curve, const uint8_t *hashes, 
 /* Batched unknown-point multiplication: out_i = k_i P_i (Section 2.1's scalar
  * multiplication of a point known only at run time, the paper's UPMUL of
  * Section 3.4 and Table 5), on any of the four curves.  Two forms:
- *  - per lane (default): one request per lane, a table of d P_i (d = 1..15)
+ *  - per lane (default): one request per lane, or per four lanes in calls of at
+ *    most 2^14 requests; a table of d P_i (d = 1..8)
  *    normalised with one Montgomery-trick chain and one Gather-Apply-Scatter
- *    inversion per workgroup, 4-bit windows of k_i in XYZZ coordinates, and
- *    one more batched inversion for the affine result;
+ *    inversion per workgroup, signed 4-bit windows of k_i (on BN254 of its two
+ *    halves under the endomorphism) with Jacobian doublings (XYZZ ones on four
+ *    lanes), and one more batched inversion for the affine result;
  *  - batched affine (ECC_PMUL_BATCHED): Algorithm 3, 256 steps over the bits
  *    of k_i from the least significant end, each an affine addition and an
  *    affine doubling per request whose denominators share one chain per lane

@@ -10,9 +10,11 @@
 // traffic per addition (two gathers of the point, prefix products, partial
 // sums), the inversion's latency and scans in each of five launches, and the
 // canonical forms that equality tests of stored points need.  Here an
-// addition reads its point once (128 B) and does nothing but its products:
-// the vector units are 90-94% busy in k_bucket_acc (3.0 10^13
-// lane-instructions/s, at the 2.0 GHz the clock settles to under them).
+// addition reads 154 B (128 of them its point) and does nothing but its products.
+// k_bucket_acc keeps the vector units busy for 0.95 of the time in a batch of 512
+// MSMs, 0.90 at BLS12-381 2^20 points (2.9 10^13 lane-instructions/s, at the 2.0 GHz
+// the clock settles to) and 0.76 at BN254 700001 points, where its two waves on a
+// SIMD leave a quarter of the issue slots open and the last items end unevenly.
 // Measured, rounds and finishing pass before against accumulation and merge
 // now: BLS12-381 2^20 points 3.39 -> 2.60 ms (a call 4.55 -> 3.50 ms), 2^16
 // 0.74 -> 0.30 ms, 512 uneven MSMs 5.04 -> 3.75 ms, BN254 700001 points 1.77 ->
@@ -315,9 +317,14 @@ __global__ void __launch_bounds__(ACC_MERGE_WG) __attribute__((amdgpu_waves_per_
   }
 }
 
-// the same with a quad of lanes in the place of a lane, for calls of at most
-// ACC_QUAD_CUTS cut buckets (1021 BLS12-381 points: 74 -> 31 us; 4096 BN254
-// points, with 6,656 buckets, take longer: 60 -> 95 us)
+// The same with a quad of lanes in the place of a lane, for calls of at most
+// ACC_QUAD_CUTS cut buckets by the plan's bound.  One MSM of the default width 8 has
+// 2,048 buckets, all of them cut (whole calls, lanes against quads: 2^10 BLS12-381
+// points 590 and 546 us, 2^15 points 834 and 798 us, 2^12 BN254 points 426 and
+// 416 us).  At 4,096 buckets of many parts the two are level (2^14 points without
+// the endomorphism 934 and 961 us); past it lanes are the faster where as many
+// buckets are really cut (2 MSMs of 2^13 points 931 and 976 us), and within 8%
+// where the bound counts many that are not.
 template <class C>
 __global__ void __launch_bounds__(ACC_MERGE_WG) k_acc_merge_quad(const AccMeta* __restrict__ meta,
                                                                  const AccCut* __restrict__ cuts, uint32_t cut_cap,
@@ -560,11 +567,13 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // one level-A wave of the plan, and its 64 quads exchange points through LDS.
 // All jobs of a workgroup have the same L (Geometry::same_chain): its threads meet
 // at barriers once per step.
-// Taken while the quads make at most two waves per SIMD, since a chain of
-// about 2 L + 13 + log2 L point operations bounds the phase there: BLS12-381,
-// 1021 points 220 -> 117 us, 2^16 points 235 -> 178 us (1.2 waves per SIMD);
-// BN254, 4096 points 107 -> 66 us.
-// Past that the quad's extra moves cost more than they save.
+// Taken while the quads make at most two waves per SIMD (512 waves of the plan on
+// this device), since a chain of about 2 L + 13 + log2 L point operations bounds the
+// phase there.  Level A, lanes against quads, by waves: 16 (1021 BLS12-381
+// points) 218 and 117 us, (4096 BN254 points) 106 and 64 us; 96 (2^12 points, c = 11)
+// 232 and 125; 320 (c = 13) 259 and 185; 416 (8 MSMs of 2^12 points) 231 and 177;
+// 640 (2^16 points, c = 14) 243 and 273; 1,024 (c = 16) 352 and 468: past the line
+// the quad's extra moves cost more than they save.
 constexpr int REDUCE_QUAD_WG = 256;
 
 template <class C>

@@ -5,7 +5,7 @@
 // with w = s^-1, u1 = e w, u2 = r w (mod n), R = u1 G + u2 Q is not O and
 // R.x mod n = r.  The paper counts a verification as one fixed-point and one
 // unknown-point multiplication (Section 5.2).  Two kernels compute it: the
-// per-lane XYZZ form at the end of this file, and first the paper's batched
+// per-lane form at the end of this file, and first the paper's batched
 // affine form, where both multiplications run in one loop over the scalar
 // bits from the least significant end, as in its batch PMUL (Section 3.4,
 // Algorithm 3):

@@ -29,7 +29,7 @@ def msm(c, bases, s, window_c=0):
 
 
 # `per` copies of one point (or its negative) in each bucket, 4 entries a part:
-# 3 parts of a bucket go to 1-4 lanes, 10 and 38 to 16, 75 and 250 to
+# 3 parts of a bucket go to 1-4 lanes, 10, 38 and 75 to 16, 250 to
 # workgroups.  3000 points at c = 13 are merged by lanes, 900 at c = 16 and 600
 # at c = 8 by quads (the second then meets the lane form of the reduction).
 @pytest.mark.parametrize("name", ["bn254", "bls12_381"])
