@@ -13,8 +13,8 @@
 // addition reads 154 B (128 of them its point) and does nothing but its products.
 // k_bucket_acc keeps the vector units busy for 0.95 of the time in a batch of 512
 // MSMs, 0.90 at BLS12-381 2^20 points (2.9 10^13 lane-instructions/s, at the 2.0 GHz
-// the clock settles to) and 0.76 at BN254 700001 points, where its two waves on a
-// SIMD leave a quarter of the issue slots open and the last items end unevenly.
+// the clock settles to) and 0.76 at BN254 700001 points (why a quarter of the issue
+// slots stays open there has not been shown).
 // Measured, rounds and finishing pass before against accumulation and merge
 // now: BLS12-381 2^20 points 3.39 -> 2.60 ms (a call 4.55 -> 3.50 ms), 2^16
 // 0.74 -> 0.30 ms, 512 uneven MSMs 5.04 -> 3.75 ms, BN254 700001 points 1.77 ->
