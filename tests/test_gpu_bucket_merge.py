@@ -64,3 +64,28 @@ def test_one_bucket_over_many_workgroups(name, n):
     assert got == dlog_msm_expected(c, k[i], s)
     # parts of at most 4 + n / 2^16 entries, whatever the bound on all windows' entries is
     assert adds <= n - n // (5 + n // 65536)
+
+
+# a captured call whose scalars change in place: cuts, lists and counters are
+# made anew on the device at every replay
+@pytest.mark.parametrize("name", ["bn254", "bls12_381"])
+def test_replays_follow_the_scalars(name):
+    c = curves.CURVES[name]
+    n = 20000
+    k, bases = seeded_bases(name, 1000, 513)
+    i = np.arange(n) % 1000
+    uniform = syn.uniform_below(514, syn.TAG_SCALARS, n, c.r, 4)
+    small = uniform & np.array([0xFF, 0, 0, 0], dtype=np.uint64)
+    ones = np.zeros_like(uniform)
+    ones[:, 0] = 1
+    b = torch.from_numpy(np.ascontiguousarray(bases[i]).view(np.int64).copy()).cuda()
+    s = torch.zeros((n, 4), dtype=torch.int64, device="cuda")
+    out = torch.zeros(2 * c.limbs, dtype=torch.int64, device="cuda")
+    inf = torch.zeros(1, dtype=torch.uint8, device="cuda")
+    with eccmi.Context(0) as ctx:
+        for values in (uniform, ones, 0 * ones, small, ones, uniform):
+            s.copy_(torch.from_numpy(values.view(np.int64).copy()))
+            eccmi.ecc_msm(ctx, c.cid, b, s, n, out, inf, flags=eccmi.ECC_USE_GRAPH)
+            torch.cuda.synchronize()
+            got = rows_to_points(c, out.cpu().numpy().view(np.uint64).reshape(1, -1), inf.cpu().numpy())[0]
+            assert got == dlog_msm_expected(c, k[i], values)
